@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsteel.so")
 SOURCES = ["steel_api.cpp", "block_index.hip", "block_select.hip", "attn_fwd.hip", "attn_ws.hip",
-           "quant_fp8.hip",
+           "attn_half.hip", "quant_fp8.hip",
            "attn_merge.hip", "noalloc.hip", "mfma_peak.hip"]
 ARCH = "gfx950"
 
@@ -35,6 +35,7 @@ COMMON = [
 # cost a copy per element), and attn_ws.hip runs two waves per SIMD, whose
 # 256 registers each hold no AGPR file.
 PER_SOURCE = {"attn_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+              "attn_half.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
               "attn_ws.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 

@@ -34,6 +34,10 @@ struct AttnArgs {
   const uint8_t* k8;        // fp8 form: E4M3 tiles of K and V (Fp8Buffers),
   const uint8_t* v8;        //   nullptr in the bf16 form
   const float* f8_scale;    //   and the per-(b, g) inverse scales {1/s_k, 1/s_v}
+  // Block mask from coordinates (every block, or with win_blocks > 0 the window
+  // and sink blocks of Problem): nothing was indexed, rows and their live lists
+  // are computed in the kernel; units: head packs (or heads) per query block
+  int coord, win_blocks, sink_blocks, units;
   int B, Hq, Hkv, S_q, S_k, nQB, nKB, G, causal, delta, R, pack;
   float c;  // scale * log2(e)
 };
@@ -51,6 +55,65 @@ __device__ __forceinline__ bool plan_matches(const AttnArgs& a) {
                   (h[kPfB] == a.B) & (h[kPfHq] == a.Hq) & (h[kPfHkv] == a.Hkv) & (h[kPfSq] == a.S_q) &
                   (h[kPfSk] == a.S_k);
   return ok;
+}
+
+// Live list of one query block.  With an index: entries beg .. beg + L - 1 of
+// col.  From coordinates: key blocks [0, a_len) and [b0, b0 + L - a_len), the
+// sink and the window (no window: all of [0, a_len)), up to the causal limit.
+struct LiveRow {
+  int L, beg, a_len, b0;
+};
+__device__ __forceinline__ LiveRow coord_row(const AttnArgs& a, int qb) {
+  LiveRow r{};
+  int kend = a.nKB;
+  if (a.causal) {
+    const long long last = (long long)min((qb + 1) * kBlk, a.S_q) - 1 + a.delta;  // last visible key
+    kend = last < 0 ? 0 : (int)min((long long)a.nKB, last / kBlk + 1);
+  }
+  if (a.win_blocks == 0) {
+    r.a_len = kend;
+    r.L = kend;
+  } else {
+    r.a_len = min(a.sink_blocks, kend);
+    r.b0 = max(r.a_len, qb - a.win_blocks + 1);
+    r.L = r.a_len + max(min(qb + 1, kend) - r.b0, 0);
+  }
+  return r;
+}
+__device__ __forceinline__ LiveRow live_row(const AttnArgs& a, int row, int qb) {
+  if (a.coord) return coord_row(a, qb);
+  LiveRow r{};
+  r.beg = ((cint_p)a.row_ptr)[row];
+  r.L = ((cint_p)a.row_ptr)[row + 1] - r.beg;
+  return r;
+}
+// Entry i < L of a live list: the key block, bit 31 set when it is partial.
+__device__ __forceinline__ uint32_t live_entry(const AttnArgs& a, const LiveRow& r, int qb, int i) {
+  if (!a.coord) return a.col[r.beg + i];
+  const int kb = i < r.a_len ? i : r.b0 + (i - r.a_len);
+  const long long end = (long long)(kb + 1) * kBlk;
+  const bool part = end > a.S_k || (a.causal && end - 1 > (long long)qb * kBlk + a.delta);
+  return (uint32_t)kb | (part ? 0x80000000u : 0u);
+}
+
+// Items of a list without an index.  Heaviest query blocks first (the live
+// count grows with the query block but for a window's first blocks), the
+// units of one query block next to each other.  The workgroups of XCD x take
+// positions 0, 1, ... of its share: with the units a multiple of 8, units x,
+// x + 8, ... (its L2 then holds the keys and values of few heads), else
+// every eighth item.  Item: unit * nQB + query block; -1 past the end.
+__device__ __forceinline__ int coord_items(const AttnArgs& a, int x) {  // of XCD x
+  const int n = a.units * a.nQB;
+  return a.units % 8 == 0 ? n / 8 : (n - x + 7) / 8;
+}
+__device__ __forceinline__ int coord_item(const AttnArgs& a, int x, int pos) {
+  if (pos >= coord_items(a, x)) return -1;
+  if (a.units % 8 == 0) {
+    const int per = a.units / 8, k = pos / per;
+    return (x + 8 * (pos - k * per)) * a.nQB + (a.nQB - 1 - k);
+  }
+  const int idx = 8 * pos + x, k = idx / a.units;
+  return (idx - k * a.units) * a.nQB + (a.nQB - 1 - k);
 }
 
 __device__ __forceinline__ float other_half_max(float x) {
@@ -150,6 +213,10 @@ template <int P> struct Par { static constexpr int value = P; };
 // Head packs of 4 at D = 128: two waves per head (scores and softmax; P V and
 // output), persistent (attn_ws.hip); prec: a Prec value.
 hipError_t launch_attention_ws(const AttnArgs& a, int prec, hipStream_t s);
+
+// bf16 forms: two waves per head, 64 query rows and half the keys of every
+// tile each (attn_half.hip); pack: heads per item of the list.
+hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, hipStream_t s);
 
 
 }  // namespace steel

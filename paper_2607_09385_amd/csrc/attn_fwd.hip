@@ -1,4 +1,5 @@
-// Fused sparse attention forward on gfx950 (bf16 MFMA, fp32 softmax state).
+// The fp8 forms of the fused sparse attention forward on gfx950, and the
+// dispatch of all forms.
 //
 // The math is the online-softmax recurrence of Algorithm 1 (Section IV):
 // for each live key block j of a query block i,
@@ -12,21 +13,18 @@
 // every wave of the workgroup.
 //
 // Layout.  Each wave owns 32 query rows.  The score tile is computed
-// transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: A = K rows from
-// LDS, B = Q rows held in VGPRs.  In the accumulator, lane l then holds query
-// row l%32 and 16 of the 32 keys of a sub-tile (key 8*(r/4) + 4*(l/32) + r%4
-// for register r), so a row's max and sum need one cross-half exchange
-// (v_permlane32_swap) instead of a 32-lane reduction, and the per-row scale
-// factors live in the same lane as the output row.  P in that layout is
-// already the B operand of O^T += V^T P^T, with the keys of each 16-key step
-// taken in the order (4 keys of this half, then the same 4 keys 8 further);
-// V^T is read from the row-major V tile with ds_read_b64_tr_b16, whose
-// 16-lane 4x16 -> 16x4 transpose delivers exactly those keys per d column.
+// transposed, S^T = K Q^T: A = K rows from LDS, B = Q rows held in VGPRs.  In
+// the accumulator, lane l then holds query row l%32 and 16 of the 32 keys of a
+// sub-tile (key 8*(r/4) + 4*(l/32) + r%4 for register r), so a row's max and
+// sum need one cross-half exchange (v_permlane32_swap) instead of a 32-lane
+// reduction, and the per-row scale factors live in the same lane as the
+// output row.  P in that layout is already the B operand of O^T += V^T P^T,
+// whose V tiles the pre-pass stores with their keys in that order.
 //
-// A workgroup handles one work item: either one (b, h, qb) query block
-// (4 waves: two row halves times two key halves of every tile) or a pack of
-// PACK query heads of one key/value group that share the same live list
-// (2*PACK waves), so each K/V tile is loaded once for up to 256 query rows.
+// A workgroup handles one work item: either one (b, h, qb) query block or a
+// pack of PACK query heads of one key/value group that share the same live
+// list, two waves per head, so each K/V tile is loaded once for up to 256
+// query rows.
 #include <climits>
 
 #include "attn_common.h"
@@ -39,19 +37,8 @@ namespace steel {
 template <int PACK>
 constexpr int stages_for() { return PACK == 1 ? 2 : 4; }
 
-// Key halves per row half: a single head in bf16 splits every tile's keys
-// over two wave pairs (see k_attn); everything else keeps whole tiles per
-// wave.
-template <int D, int PACK, int PREC, bool RAGGED>
-constexpr int key_halves() { return PACK == 1 && PREC == kBf16 ? 2 : 1; }
-template <int D, int PACK, int PREC, bool RAGGED>
-constexpr int attn_threads() { return 128 * PACK * key_halves<D, PACK, PREC, RAGGED>(); }
-// Waves per SIMD the register allocation must allow: the key-split D = 64
-// kernel is built for four (128 VGPRs), so that four of its workgroups (16
-// waves, the 2-stage rings filling 128 KiB of LDS) share a CU; 1 leaves the
-// allocation free.
-template <int D, int PACK, int PREC, bool RAGGED>
-constexpr int attn_min_waves() { return D == 64 && key_halves<D, PACK, PREC, RAGGED>() == 2 ? 4 : 1; }
+template <int PACK>
+constexpr int attn_threads() { return 128 * PACK; }
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
@@ -71,96 +58,24 @@ __device__ __forceinline__ f32x16 mfma_e4m3(const i32x8& a, const i32x8& b, cons
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
 
-// End of a key-split single-head workgroup: the waves of the two key halves of
-// one row half hold (m_h, l_h, O_h) over their keys, with O_h = sum 2^(s - m_h) v
-// and l_h the sum of the same weights.  With M = max(m_0, m_1) and
-// w_h = 2^(m_h - M) (0 for a half that saw no key) the row's state is
-// l = w_0 l_0 + w_1 l_1, O = w_0 O_0 + w_1 O_1.  Each wave finishes half of the
-// d tiles: it leaves the other half of its O, its m and its row sum in LDS
-// (free once the loop's last barrier has passed), and reads its partner's.
-// LDS per record: [field][lane] floats, record (row half, key half).
-template <int D>
-__device__ __forceinline__ void merge_halves(const AttnArgs& a, f32x16 (&o)[D / 32], float m,
-                                             float l, int kh, int rh, int lane, float* xs, int b,
-                                             int head, int qrow0, int hf) {
-  constexpr int DT = D / 32, HD = DT / 2;  // d tiles, d tiles finished per wave
-  constexpr int F = 2 + 16 * HD;           // fields per record
-  const float lt = half_pair_sum(l);
-  float* mine = xs + (rh * 2 + kh) * F * 64 + lane;
-  const float* part = xs + (rh * 2 + (kh ^ 1)) * F * 64 + lane;
-  // d tiles [0, HD) are finished by key half 0, [HD, DT) by key half 1 (the
-  // register array is only indexed by constants: selects, not scratch)
-  mine[0] = m;
-  mine[64] = lt;
-#pragma unroll
-  for (int j = 0; j < HD; ++j) {
-    const f32x16 give = kh ? o[j] : o[HD + j];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mine[(2 + 16 * j + r) * 64] = give[r];
-  }
-  __syncthreads();
-  const float mp = part[0], ltp = part[64];
-  const float M = fmaxf(m, mp);
-  const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
-  const float wp = mp == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mp - M);
-  const float ls = w * lt + wp * ltp;
-  const float inv = ls > 0.f ? 1.f / ls : 0.f;
-  const int qrow = qrow0;
-  if (qrow >= a.S_q) return;
-  // log sum_j exp(scale s_ij) = (M + log2 l) ln 2 (Algorithm 1's statistics)
-  if (a.lse != nullptr && hf == 0 && kh == 0)
-    a.lse[((size_t)b * a.Hq + head) * a.S_q + qrow] =
-        ls > 0.f ? (M + log2f(ls)) * 0.69314718055994531f : -INFINITY;
-  const size_t at = (((size_t)b * a.Hq + head) * a.S_q + qrow) * D + 4 * hf;
-#pragma unroll
-  for (int j = 0; j < HD; ++j) {
-    const int dt = kh * HD + j;
-    const f32x16 keep = kh ? o[HD + j] : o[j];
-#pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      f32x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 4 * gq + e;
-        v[e] = (w * keep[r] + wp * part[(2 + 16 * j + r) * 64]) * inv;
-      }
-      if (a.out_bf16) {
-        const bf16x4 vb = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-        *(bf16x4*)((__bf16*)a.out + at + 32 * dt + 8 * gq) = vb;
-      } else {
-        *(f32x4*)(a.out + at + 32 * dt + 8 * gq) = v;
-      }
-    }
-  }
-}
-
 // Workgroup = PACK heads x 64 query rows.  Each wave owns 32 query rows (one
 // 32-row MFMA N-tile) of one head, two waves per head, so that two waves
 // share each SIMD and one can issue MFMAs while the other computes
-// exponentials.  A single head at D = 128 (whose register use allows one
-// such workgroup per SIMD pair only) would leave one wave per SIMD, so there
-// the keys of every tile are split as well: waves 0-1 take keys 0-31, waves
-// 2-3 keys 32-63, each with its own softmax state, and the two states of a
-// row are merged at the end (the split-key form of the same recurrence, exact
-// up to rounding).  A single head at D = 64 splits its keys the same way:
-// each wave then holds half the scores and fits in 128 VGPRs, so four waves
-// share each SIMD (twice the softmax issue of the two-wave form, whose four
-// workgroups per CU left two per SIMD).
-// RAGGED: S_k is not a multiple of the block (the
-// tail block's copies clamp their rows); without it that path is compiled out.
+// exponentials.  The operands of P V are E4M3, those of the scores E4M3
+// (PREC = kFp8All) or bf16 (kFp8Pv).
+// RAGGED: S_k is not a multiple of the block (the tail block's bf16 copies
+// clamp their rows); without it that path is compiled out.
 template <int D, int PACK, bool RAGGED, int PREC>
-__global__ __launch_bounds__((attn_threads<D, PACK, PREC, RAGGED>()))
-__attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) void k_attn(AttnArgs a) {
+__global__ __launch_bounds__(attn_threads<PACK>()) void k_attn(AttnArgs a) {
   constexpr bool QK8 = PREC == kFp8All;  // S = K Q^T from E4M3 operands
-  constexpr bool PV8 = PREC != kBf16;    // O += V P from E4M3 operands
+  static_assert(PREC != kBf16, "the bf16 forms are k_attn_h and k_attn_ws");
   constexpr int NT = 1;            // 32-row N-tiles per wave
-  constexpr int KH = key_halves<D, PACK, PREC, RAGGED>();  // key halves (waves per 32 rows)
-  constexpr int NSG = 2 / KH;      // 32-key sub-tiles per wave and tile
-  constexpr int NW = PACK * 2 * KH;  // waves
+  constexpr int NSG = 2;           // 32-key sub-tiles per tile
+  constexpr int NW = PACK * 2;     // waves
   constexpr int C = D / 8;         // 16-byte chunks per bf16 row
   constexpr int TE = kBlk * D;     // elements per tile
   constexpr int TB8 = TE;          // bytes of an E4M3 tile
-  constexpr int TBK = QK8 ? TB8 : 2 * TE, TBV = PV8 ? TB8 : 2 * TE;  // K, V tile bytes
+  constexpr int TBK = QK8 ? TB8 : 2 * TE, TBV = TB8;  // K, V tile bytes
   constexpr int SB = TBK + TBV;    // bytes per ring stage
   // 16-byte copies per lane per tile: bf16 tiles LPW from every wave; E4M3
   // tiles LPW8 from the first CW8 waves
@@ -168,14 +83,12 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   constexpr int LPW8 = TB8 / 16 >= 64 * NW ? TB8 / 16 / (64 * NW) : 1;
   constexpr int CW8 = TB8 / 16 / (64 * LPW8);
   // copy instructions per lane per tile of waves below CW8 and of the others
-  constexpr int CPT_LO = (QK8 ? LPW8 : LPW) + (PV8 ? LPW8 : LPW);
-  constexpr int CPT_HI = (QK8 ? 0 : LPW) + (PV8 ? 0 : LPW);
+  constexpr int CPT_LO = (QK8 ? LPW8 : LPW) + LPW8;
+  constexpr int CPT_HI = QK8 ? 0 : LPW;
   constexpr int KS = D / 16;       // k-steps of S^T = K Q^T (bf16)
   constexpr int KS8 = D / 64;      // k-steps of S^T = K Q^T (fp8)
   constexpr int DT = D / 32;       // d tiles of O^T
-  // bf16 P: rescale only when the row max grows by > 2^8; E4M3 P: on every
-  // growth (its weights need the exact maximum, see the P step)
-  constexpr float TAU = PV8 ? 0.0f : 8.0f;
+  // E4M3 P needs the exact running maximum: rescale on every growth
   static_assert(LPW >= 1 && C % NW == 0 && CW8 >= 1 && CW8 <= NW && CW8 * 64 * LPW8 * 16 == TB8,
                 "tile copy split");
   // A ring of ST stages, each holding the K and the V tile of one key block:
@@ -185,7 +98,10 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
 
   // index data is read-only during the kernel: scalar loads
   int item;
-  if (PACK == 1 && a.bucket != nullptr) {
+  if (a.coord) {
+    item = coord_item(a, (int)blockIdx.x & 7, (int)blockIdx.x >> 3);
+    if (item < 0) return;
+  } else if (PACK == 1 && a.bucket != nullptr) {
     // single-head items: workgroup b runs on XCD b % 8 and takes the
     // (b / 8)-th item of that XCD's bucket (heaviest first within it).  The
     // bucket bounds (always present) and the plan header are read together,
@@ -211,18 +127,15 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   const int g = h0 / a.G;
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int kh = KH == 1 ? 0 : wave >> 1;  // key half of this wave
-  const int head = h0 + (KH == 1 ? wave >> 1 : 0);
+  const int head = h0 + (wave >> 1);
   const int n = lane & 31, hf = lane >> 5;
   const int qrow0 = qb * kBlk + (wave & 1) * 32 + n;  // N-tile nt holds row qrow0 + 32*nt
 
   const int r0 = bh0 * a.nQB + qb;
-  const int beg = ((cint_p)a.row_ptr)[r0];
-  const int L = ((cint_p)a.row_ptr)[r0 + 1] - beg;
-  const cuint_p colp = (cuint_p)a.col + beg;
+  const LiveRow lr = live_row(a, r0, qb);
+  const int L = lr.L;
   const size_t kvoff = ((size_t)b * a.Hkv + g) * a.S_k * D;
   const __bf16* kg = a.k + kvoff;
-  const __bf16* vg = a.v + kvoff;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
 
   // copy plan: copy j of this lane fills tile slot (wave*LPW + j)*64 + lane,
@@ -271,8 +184,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
     const uint32_t at = (uint32_t)st * SB;
     if constexpr (QK8) issue_copy8(a.k8, at, kb);
     else issue_copy(kg, at, kb);
-    if constexpr (PV8) issue_copy8(a.v8, at + TBK, kb);
-    else issue_copy(vg, at + TBK, kb);
+    issue_copy8(a.v8, at + TBK, kb);
   };
 
   // Per-lane LDS read offsets in bytes (tile buffer base and the row block of
@@ -280,21 +192,9 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   //   K fragment (sg, ks): row 32*sg + n, chunk (2*ks + hf)
   //   V fragment (sg, t, cc, dt): row 32*sg + 16*t + 8*cc + 4*(tg>>1) + tr,
   //                               chunk 4*dt + 2*(tg&1) + (tq>>1), half tq&1
-  const uint32_t half_off = (uint32_t)(kh * 32 * D * 2);
   uint32_t koff[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) koff[ks] = (uint32_t)tile_elem<D>(n, 2 * ks + hf) * 2 + half_off;
-  const int tg = lane >> 4, tr = (lane >> 2) & 3, tq = lane & 3;
-  uint32_t voff[2][DT];
-#pragma unroll
-  for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      const int row = 8 * cc + 4 * (tg >> 1) + tr;
-      voff[cc][dt] =
-          (uint32_t)(tile_elem<D>(row, 4 * dt + 2 * (tg & 1) + (tq >> 1)) + 4 * (tq & 1)) * 2 + half_off;
-    }
-
+  for (int ks = 0; ks < KS; ++ks) koff[ks] = (uint32_t)tile_elem<D>(n, 2 * ks + hf) * 2;
   // Prologue.  Tile 0 is copied in while Q is fetched; the Q fragments are
   // then consumed by an empty asm statement, which makes the compiler wait for
   // its Q loads here, before the loop (and with them for tile 0, issued
@@ -302,7 +202,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   // the loop, where it would drain every in-flight copy on each iteration.
   // Only then are tiles 1 .. ST-2 put in flight.  Stage s holds K at byte
   // offset s*SB and V at s*SB + TBK.
-  if (L > 0) copy_kv(0, (int)(colp[0] & 0x7fffffffu));
+  if (L > 0) copy_kv(0, (int)(live_entry(a, lr, qb, 0) & 0x7fffffffu));
 
   // Q rows as the B operand: N-tile nt, lane holds row 32*nt + n, d = 16*ks + 8*hf + 0..7
   bf16x8 qf[QK8 ? 1 : NT][QK8 ? 1 : KS];
@@ -311,7 +211,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   // factor from the MFMA scores to log2 units, scale*log2(e) / (s_q s_k)
   i32x8 q8[NT][QK8 ? KS8 : 1];
   float cr[NT];
-  const float dv = PV8 ? a.f8_scale[2 * ((size_t)b * a.Hkv + g) + 1] : 1.f;
+  const float dv = a.f8_scale[2 * ((size_t)b * a.Hkv + g) + 1];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const __bf16* qrow =
@@ -347,9 +247,8 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   // The live list is kept in two VGPRs (entries 64j .. 64j+127, one per
   // lane) and entries are extracted with v_readlane.  Scalar loads inside the
   // loop would make every LDS wait an lgkmcnt(0) wait for them.
-  const uint32_t* colv = a.col + beg;
   auto load_win = [&](int base) -> uint32_t {
-    return base + lane < L ? colv[base + lane] : 0u;
+    return base + lane < L ? live_entry(a, lr, qb, base + lane) : 0u;
   };
   int wbase = 0;
   uint32_t win0 = load_win(0), win1 = load_win(64);
@@ -368,7 +267,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
 
 #pragma unroll
   for (int s = 1; s < ST - 1; ++s)
-    if (s < L) copy_kv(s, (int)(colp[s] & 0x7fffffffu));
+    if (s < L) copy_kv(s, (int)(live_entry(a, lr, qb, s) & 0x7fffffffu));
 
   f32x16 o[NT][DT];
   float m[NT], l[NT];
@@ -383,12 +282,6 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
   const char* lds_bytes = (const char*)smem;
   auto ld_k = [&](int S, int sg, int ks) -> bf16x8 {
     return *(const bf16x8*)(lds_bytes + S * SB + sg * 32 * D * 2 + koff[ks]);
-  };
-  auto ld_v = [&](int S, int sg, int t, int dt) -> bf16x8 {
-    const char* base = lds_bytes + S * SB + TBK + (32 * sg + 16 * t) * D * 2;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + voff[0][dt]));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + voff[1][dt]));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   // fp8 operand reads (layouts of Fp8Buffers): K fragment (sg, ks8) = row
   // 32*sg + n, logical chunks 4*ks8 + 2*hf + {0, 1}; V fragment dt = row
@@ -477,7 +370,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const int lim_abs = min(a.causal ? qrow0 + 32 * nt + a.delta : INT_MAX - kBlk, a.S_k - 1);
-        const int lim = lim_abs - (kb * kBlk + 4 * hf + 32 * kh);
+        const int lim = lim_abs - (kb * kBlk + 4 * hf);
 #pragma unroll
         for (int sg = 0; sg < NSG; ++sg)
 #pragma unroll
@@ -501,10 +394,9 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[nt][sg][r]);
       mx = other_half_max(mx);
       mt[nt] = mx == -INFINITY ? -INFINITY : mx * cr[nt];
-      grow |= mt[nt] > m[nt] + TAU;
+      grow |= mt[nt] > m[nt];
     }
-    // Rescale only when some row's maximum grew by more than TAU (log2
-    // units): P = 2^(S - m) then stays below 2^TAU, and m cancels in O / l.
+    // rescale when some row's maximum grew (m stays the exact running maximum)
     if (__builtin_amdgcn_ballot_w64(grow)) {
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
@@ -520,7 +412,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) msafe[nt] = m[nt] == -INFINITY ? 0.f : m[nt];
 
-    if constexpr (PV8) {
+    {
       // P = 2^(S - m + 8) in (0, 2^8] (m is the exact running maximum):
       // rounded to E4M3 for the product, summed before rounding into l; the
       // lane's 32 weights in the operand's byte order b = 16*sg + r
@@ -545,45 +437,6 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) o[nt][dt] = mfma_e4m3(vf, p8[nt], o[nt][dt]);
       }
-    } else {
-
-    // P.V in 2*NSG phases, one per 16-key chunk k = (sg, t): phase k runs the
-    // MFMAs of chunk k while the exponentials of chunk k+1 are computed and
-    // the V fragments of chunk k+1 are read.  The row sums add the
-    // bf16-rounded P that the MFMAs consume (v_dot2 against (1, 1)), so
-    // O / l weights the value rows exactly as used.
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    auto exps = [&](int k, bf16x8* p) {
-      const int sg = k >> 1, t = k & 1;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          p[nt][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[nt][sg][8 * t + e], a.c, -msafe[nt]));
-#pragma unroll
-        for (int e = 0; e < 8; e += 2)
-          l[nt] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{p[nt][e], p[nt][e + 1]}, ones, l[nt], false);
-      }
-    };
-    bf16x8 vf[2][DT], pa[2][NT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[0][dt] = ld_v(S, 0, 0, dt);
-    exps(0, pa[0]);
-    constexpr int NCH = 2 * NSG;
-#pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-      const int cur = k & 1, nx = cur ^ 1;
-      if (k + 1 < NCH) {
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) vf[nx][dt] = ld_v(S, (k + 1) >> 1, (k + 1) & 1, dt);
-        exps(k + 1, pa[nx]);
-      }
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[cur][dt], pa[cur][nt], o[nt][dt], 0, 0, 0);
-    }
     }
 
     // tile i+1 must have landed before the barrier: newer copies (tiles
@@ -621,10 +474,6 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
     }
   }
 
-  if constexpr (KH == 2) {
-    merge_halves<D>(a, o[0], m[0], l[0], kh, wave & 1, lane, (float*)smem, b, head, qrow0, hf);
-    return;
-  }
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const int qrow = qrow0 + 32 * nt;
@@ -634,7 +483,7 @@ __attribute__((amdgpu_waves_per_eu(attn_min_waves<D, PACK, PREC, RAGGED>()))) vo
     // log sum_j exp(scale s_ij) = (m + log2 l) ln 2: m in log2 units, l the
     // row sum relative to 2^m (Algorithm 1's statistics; the fp8 weights
     // carry an extra 2^8)
-    constexpr float m_off = PV8 ? 8.f : 0.f;
+    constexpr float m_off = 8.f;
     if (a.lse != nullptr && hf == 0 && qrow < a.S_q)
       a.lse[((size_t)b * a.Hq + head) * a.S_q + qrow] =
           lt > 0.f ? (m[nt] - m_off + log2f(lt)) * 0.69314718055994531f : -INFINITY;
@@ -661,23 +510,20 @@ template <int D, int PACK, int PREC>
 static void launch_one(const AttnArgs& a, int grid, hipStream_t s) {
   if (grid <= 0) return;
   // the bucket-dealt single-head list: grid is already 8 x (largest bucket)
-  const int g = PACK == 1 && a.bucket != nullptr ? grid : xcd_grid(grid);
+  const int g = PACK == 1 && (a.coord || a.bucket != nullptr) ? grid : xcd_grid(grid);
   // E4M3 tiles are padded with zero keys: with both tensors in E4M3 no copy
-  // clamps.  The whole-tile D = 64 kernels keep the ragged copy for every
-  // S_k: without it they need fewer registers, a third wave fits on each
-  // SIMD, and the two-wave single-head kernel ran 4.6% slower that way on
-  // the 24-head S = 32768 workload.  The key-split single-head D = 64 kernel
-  // has its own register budget.
-  constexpr bool kRaggedAlways = D == 64 && !(PACK == 1 && PREC == kBf16);
+  // clamps.  The D = 64 kernels keep the ragged copy for every S_k: without
+  // it they need fewer registers and a third wave per SIMD ran slower.
+  constexpr bool kRaggedAlways = D == 64;
   if constexpr (PREC == kFp8All)
     hipLaunchKernelGGL((k_attn<D, PACK, false, PREC>), dim3(g),
-                       dim3(attn_threads<D, PACK, PREC, false>()), 0, s, a);
+                       dim3(attn_threads<PACK>()), 0, s, a);
   else if (kRaggedAlways || a.S_k % kBlk != 0)
     hipLaunchKernelGGL((k_attn<D, PACK, true, PREC>), dim3(g),
-                       dim3(attn_threads<D, PACK, PREC, true>()), 0, s, a);
+                       dim3(attn_threads<PACK>()), 0, s, a);
   else
     hipLaunchKernelGGL((k_attn<D, PACK, false, PREC>), dim3(g),
-                       dim3(attn_threads<D, PACK, PREC, false>()), 0, s, a);
+                       dim3(attn_threads<PACK>()), 0, s, a);
 }
 
 template <int D, int PREC>
@@ -685,28 +531,32 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
   if (p.pack > 1) {
     AttnArgs ap = a;
     ap.order = w.order_p;
-    ap.n_items = w.n_items + kPackItems;  // 0 when k_bucket handed them to the single-head list
-    if (p.pack == 2) {
-      launch_one<D, 2, PREC>(ap, p.NP, s);
-    } else if (D == 128 && (size_t)p.S_q * D * 4 < (1ull << 31)) {
-      const hipError_t e = launch_attention_ws(ap, PREC, s);
-      if (e != hipSuccess) return e;
-    } else {
-      launch_one<D, 4, PREC>(ap, p.NP, s);
-    }
+    ap.n_items = a.coord ? nullptr : w.n_items + kPackItems;  // 0 when k_bucket handed them to the single-head list
+    ap.units = p.B * (p.Hq / p.pack);
+    hipError_t e = hipSuccess;
+    if (D == 128 && p.pack == 4 && (size_t)p.S_q * D * 4 < (1ull << 31) && (PREC != kBf16 || p.NP > kFewPacks))
+      e = launch_attention_ws(ap, PREC, s);
+    else if constexpr (PREC == kBf16) e = launch_attention_half(ap, D, p.pack, p.NP, s);
+    else if (p.pack == 2) launch_one<D, 2, PREC>(ap, p.NP, s);
+    else launch_one<D, 4, PREC>(ap, p.NP, s);
+    if (e != hipSuccess) return e;
   }
   if (p.pack > 1 && p.heads_share_mask) return hipGetLastError();  // no single-head item
   a.order = w.order_s;
   a.n_items = w.n_items;
   a.bucket = w.bucket;
+  a.units = p.B * p.Hq;
   int grid = p.R;
-  if (w.bucket != nullptr) {
+  if (a.coord) {
+    grid = (p.R + 7) / 8 * 8;
+  } else if (w.bucket != nullptr) {
     // at most the rows of the key/value heads of one bucket: nQB * G rows per
     // head, ceil(B*Hkv / 8) heads per bucket
     const long long per = (long long)p.nQB * p.G * ((p.B * p.Hkv + kBuckets - 1) / kBuckets);
     grid = (int)(kBuckets * per);
   }
-  launch_one<D, 1, PREC>(a, grid, s);
+  if constexpr (PREC == kBf16) return launch_attention_half(a, D, 1, grid, s);
+  else launch_one<D, 1, PREC>(a, grid, s);
   return hipGetLastError();
 }
 
@@ -724,11 +574,15 @@ hipError_t launch_attention(const Problem& p, const void* q, const void* k, cons
   a.col = w.col;
   a.order = nullptr;
   a.n_items = nullptr;
-  a.header = w.n_items + kPlanAt;
+  a.header = p.coord ? nullptr : w.n_items + kPlanAt;
   a.bucket = nullptr;
   a.k8 = p.fp8 ? f.k8 : nullptr;
   a.v8 = p.fp8 ? f.v8 : nullptr;
   a.f8_scale = p.fp8 ? f.scale : nullptr;
+  a.coord = p.coord;
+  a.win_blocks = p.win_blocks;
+  a.sink_blocks = p.sink_blocks;
+  a.units = 0;
   a.nKB = p.nKB;
   a.B = p.B;
   a.R = p.R;

@@ -160,8 +160,8 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
 
-  if (!plan_matches(a)) return;  // index planned for another problem: out untouched
-  const int n_all = ((cint_p)a.n_items)[0];
+  if (!a.coord && !plan_matches(a)) return;  // index planned for another problem: out untouched
+  const int n_all = a.coord ? 0 : ((cint_p)a.n_items)[0];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -176,8 +176,9 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   struct Item {
     int L, beg, qb, b, h0;
   };
-  const int n_x = (n_all / (8 * GROUP)) * GROUP +
-                  min(max(n_all % (8 * GROUP) - GROUP * xb, 0), GROUP);
+  const int n_x = a.coord ? coord_items(a, xb)
+                          : (n_all / (8 * GROUP)) * GROUP +
+                                min(max(n_all % (8 * GROUP) - GROUP * xb, 0), GROUP);
   const int K = (n_x + nwb - 1) / nwb;  // rounds of this XCD
   // round k of this workgroup: position r*nwb + w (even r) or r*nwb + nwb-1-w
   // (odd r) of the XCD's share of the work order, rounds in the order K-1,
@@ -193,15 +194,22 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   int w_item = -1, w_beg = 0, w_end = 0;
   auto load_items = [&](int win) __attribute__((always_inline)) {
     const int p = round_pos(64 * win + lane);
-    const int idx = p < 0 ? n_all : xcd_slot<GROUP>(8 * p + xb);
     w_item = -1;
     w_beg = 0;
     w_end = 0;
-    if (idx < n_all) {
-      w_item = a.order[idx];
-      const int r0 = (w_item / a.nQB) * 4 * a.nQB + w_item % a.nQB;
-      w_beg = a.row_ptr[r0];
-      w_end = a.row_ptr[r0 + 1];
+    if (a.coord) {
+      if (p >= 0) {
+        w_item = coord_item(a, xb, p);
+        w_end = coord_row(a, w_item % a.nQB).L;
+      }
+    } else {
+      const int idx = p < 0 ? n_all : xcd_slot<GROUP>(8 * p + xb);
+      if (idx < n_all) {
+        w_item = a.order[idx];
+        const int r0 = (w_item / a.nQB) * 4 * a.nQB + w_item % a.nQB;
+        w_beg = a.row_ptr[r0];
+        w_end = a.row_ptr[r0 + 1];
+      }
     }
     asm volatile("" ::"v"(w_item), "v"(w_beg), "v"(w_end));
     iw = win;
@@ -221,7 +229,11 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
     return true;
   };
   auto load_entry_vec = [&](const Item& it, int base) __attribute__((always_inline)) -> uint32_t {
-    return base + lane < it.L ? a.col[it.beg + base + lane] : 0u;
+    if (base + lane >= it.L) return 0u;
+    LiveRow r{};
+    if (a.coord) r = coord_row(a, it.qb);
+    else r.beg = it.beg;
+    return live_entry(a, r, it.qb, base + lane);
   };
   auto kv_tile8 = [&](const Item& it) __attribute__((always_inline)) -> size_t {
     return ((size_t)it.b * a.Hkv + it.h0 / a.G) * a.nKB;

@@ -41,6 +41,9 @@ struct Problem {
   // mask tensor, or the structured mask): with pack > 1 every head pack is
   // then uniform and the single-head list is empty, so it is not launched.
   int heads_share_mask;
+  // Set by the fused calls without a mask tensor: the attention kernels compute
+  // rows and live lists from the coordinates, and no index is built.
+  int coord;
   int out_bf16;  // output in bf16 (RNE of the fp32 result) instead of fp32
   int fp8;       // operand precision of the products: a Prec value
 };
@@ -147,6 +150,10 @@ constexpr int kHeaderInts = kPackItems + 1;
 // live list, so either kernel computes the same rows.
 constexpr int kDemotePacks = 64;
 constexpr int kDemoteMinSingle = 1024;
+
+// Up to this many head packs of 4 at D = 128 (bf16) are run two heads to a
+// workgroup instead of four: a persistent workgroup per CU leaves CUs idle.
+constexpr int kFewPacks = 256;
 
 __host__ __device__ inline int nchunks(int n) { return (n + kChunk - 1) / kChunk; }
 
