@@ -190,19 +190,21 @@ Layout layout(const steel::Problem& p, bool with_rowptr_col_order) {
     off += align256(bytes);
     return at;
   };
-  const size_t nch_s = steel::nchunks(p.R);
-  const size_t nch_p = p.pack > 1 ? steel::nchunks(p.NP) : 0;
-  L.cnt = take(sizeof(int32_t) * p.R);
-  L.hist_s = take(sizeof(int32_t) * steel::kBins * nch_s);
-  L.hist_p = take(sizeof(int32_t) * (nch_p ? steel::kBins * nch_p : 1));
-  L.n_items = take(sizeof(int32_t) * steel::kHeaderInts);
-  L.order_p = take(sizeof(int32_t) * (p.NP > 0 ? p.NP : 1));
-  if (with_rowptr_col_order) {
-    L.row_ptr = take(sizeof(int32_t) * (p.R + 1));
-    L.col = take(sizeof(uint32_t) * (size_t)p.R * p.nKB);
-    L.order_s = take(sizeof(int32_t) * p.R);
-    L.bucket = take(sizeof(int32_t) * ((size_t)p.R + steel::kBuckets + 1));
-    L.has_bucket = true;
+  if (!p.coord) {  // without a mask tensor nothing is indexed
+    const size_t nch_s = steel::nchunks(p.R);
+    const size_t nch_p = p.pack > 1 ? steel::nchunks(p.NP) : 0;
+    L.cnt = take(sizeof(int32_t) * p.R);
+    L.hist_s = take(sizeof(int32_t) * steel::kBins * nch_s);
+    L.hist_p = take(sizeof(int32_t) * (nch_p ? steel::kBins * nch_p : 1));
+    L.n_items = take(sizeof(int32_t) * steel::kHeaderInts);
+    L.order_p = take(sizeof(int32_t) * (p.NP > 0 ? p.NP : 1));
+    if (with_rowptr_col_order) {
+      L.row_ptr = take(sizeof(int32_t) * (p.R + 1));
+      L.col = take(sizeof(uint32_t) * (size_t)p.R * p.nKB);
+      L.order_s = take(sizeof(int32_t) * p.R);
+      L.bucket = take(sizeof(int32_t) * ((size_t)p.R + steel::kBuckets + 1));
+      L.has_bucket = true;
+    }
   }
   if (p.fp8) {
     const size_t tiles = (size_t)p.B * p.Hkv * p.nKB * steel::kBlk * p.D;  // bytes per tensor
@@ -282,12 +284,18 @@ int check_workspace(const void* ws, size_t bytes, const Layout& L) {
   return STEEL_OK;
 }
 
-// The fused call once the arguments are checked: the device's scratch buffer,
-// index build, attention.
+// The fused call once the arguments are checked: the stream's scratch buffer,
+// index build, attention.  Without a mask tensor there is no index, and in
+// bf16 no scratch: the attention kernels are all of the call.
 int fused_call(const steel::Problem& p, const void* q, const void* k, const void* v,
                const uint8_t* block_mask, void* out, float* lse, float scale, void* stream) {
   int rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (p.coord && !p.fp8) {  // no index, no operands: nothing to keep
+    const hipError_t e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale,
+                                                 steel::IndexBuffers{}, steel::Fp8Buffers{}, s);
+    return e == hipSuccess ? STEEL_OK : hip_fail(e, "launching kernels");
+  }
   int dev = 0;
   if ((rc = stream_device(s, &dev)) != STEEL_OK) return rc;
   const Layout L = layout(p, true);
@@ -295,7 +303,7 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
   StreamScratch* slot = nullptr;
   char* ws = nullptr;
   if ((rc = scratch_begin(dev, s, L.total, &lk, &slot, &ws)) != STEEL_OK) return rc;
-  const steel::IndexBuffers w = carve(ws, L);
+  const steel::IndexBuffers w = p.coord ? steel::IndexBuffers{} : carve(ws, L);
   steel::Fp8Buffers f{};
   if (p.fp8) {
     f.k8 = p.fp8 == steel::kFp8All ? reinterpret_cast<uint8_t*>(ws + L.k8) : nullptr;
@@ -303,7 +311,7 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
     f.part = reinterpret_cast<float*>(ws + L.f8_part);
     f.scale = reinterpret_cast<float*>(ws + L.f8_scale);
   }
-  hipError_t e = steel::launch_block_index(p, block_mask, w, s);
+  hipError_t e = p.coord ? hipSuccess : steel::launch_block_index(p, block_mask, w, s);
   if (e == hipSuccess && p.fp8) e = steel::launch_fp8_prepass(p, k, v, f, s);
   if (e == hipSuccess)
     e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale, w, f, s);
@@ -328,7 +336,7 @@ int steel_attn_fwd(const void* q, const void* k, const void* v, const uint8_t* b
   int rc = check_attn(q, k, v, out, B, Hq, Hkv, S_q, S_k, D, blk, scale, causal, &p);
   if (rc != STEEL_OK) return rc;
   set_pack(&p);
-  p.heads_share_mask = block_mask == nullptr;
+  p.heads_share_mask = p.coord = block_mask == nullptr;
   return fused_call(p, q, k, v, block_mask, out, nullptr, scale, stream);
 }
 
@@ -341,7 +349,7 @@ int steel_attn_fwd_window(const void* q, const void* k, const void* v, void* out
   if (rc != STEEL_OK) return rc;
   if ((rc = set_window(&p, window_blocks, sink_blocks)) != STEEL_OK) return rc;
   set_pack(&p);
-  p.heads_share_mask = 1;
+  p.heads_share_mask = p.coord = 1;
   return fused_call(p, q, k, v, nullptr, out, nullptr, scale, stream);
 }
 
@@ -364,7 +372,7 @@ int steel_attn_fwd_ex(const void* q, const void* k, const void* v, const uint8_t
   p.out_bf16 = (flags & STEEL_OUT_BF16) != 0;
   p.fp8 = (flags & STEEL_FP8) ? steel::kFp8All : (flags & STEEL_FP8_PV) ? steel::kFp8Pv : steel::kBf16;
   set_pack(&p);
-  p.heads_share_mask = block_mask == nullptr;
+  p.heads_share_mask = p.coord = block_mask == nullptr;
   return fused_call(p, q, k, v, block_mask, out, lse, scale, stream);
 }
 
@@ -377,12 +385,13 @@ int steel_attn_fwd_noalloc(const void* q, const void* k, const void* v,
   if (rc != STEEL_OK) return rc;
   set_pack(&p);
   p.heads_share_mask = block_mask == nullptr;
-  const Layout L = layout(p, true);
+  const Layout L = layout(p, true);  // the limit is that of the index, needed or not
   if (L.total > steel::kNoAllocBytes)
     return fail(STEEL_ERR_UNSUPPORTED,
                 "the index of this problem needs %zu bytes of scratch; steel_attn_fwd_noalloc "
                 "holds %zu (use steel_attn_fwd or plan/run)",
                 L.total, steel::kNoAllocBytes);
+  p.coord = block_mask == nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   int dev = 0;
   if ((rc = stream_device(s, &dev)) != STEEL_OK) return rc;
@@ -390,7 +399,7 @@ int steel_attn_fwd_noalloc(const void* q, const void* k, const void* v,
   hipError_t e = steel::noalloc_scratch(dev, &ws);
   if (e != hipSuccess) return hip_fail(e, "looking up the fixed scratch array");
   const steel::IndexBuffers w = carve(ws, L);
-  e = steel::launch_block_index(p, block_mask, w, s);
+  e = p.coord ? hipSuccess : steel::launch_block_index(p, block_mask, w, s);
   if (e == hipSuccess)
     e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), nullptr, scale, w,
                                 steel::Fp8Buffers{}, s);
