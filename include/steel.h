@@ -78,6 +78,13 @@ typedef enum steel_status {
  * synchronous; the stream's earlier calls are waited for) when a call needs
  * more than it holds; it is kept until the process ends.  Results are
  * bitwise reproducible run to run.
+ *
+ * Without a mask tensor nothing is indexed and, unless the lists are split,
+ * no scratch is used.  Calls without a mask tensor whose query blocks are too
+ * few to fill the GPU (decoding, a few queries against many keys; S_k > 960)
+ * run every live list in segments and add the partial results in fp32, and
+ * heads of one group whose rows fit one block together as one item: the same
+ * sums in another order.
  */
 int steel_attn_fwd(const void* q, const void* k, const void* v,
                    const uint8_t* block_mask, void* out,
@@ -116,8 +123,8 @@ int steel_block_index(const uint8_t* block_mask, int B, int Hq, int S_q, int S_k
  * Two-phase form of steel_attn_fwd for callers that reuse one mask over many
  * calls (for example every layer of a model): steel_attn_plan builds the
  * live-block index once into caller-owned device workspace, steel_attn_run
- * runs the fused pass over it.  plan + run computes exactly what
- * steel_attn_fwd computes.
+ * runs the fused pass over it.  plan + run computes what steel_attn_fwd
+ * computes, bit for bit unless that call splits its lists (see there).
  *
  *   steel_attn_workspace_bytes  size of the workspace for these sizes, or 0
  *                               after an argument error (see
@@ -232,8 +239,9 @@ int steel_attn_merge(const float* o_parts, const float* lse_parts, int n_parts, 
  *     qb - window_blocks < kb <= qb      (window ending at the block diagonal)
  *  or kb < sink_blocks                   (sink blocks at the start)
  * and the causal structure is then applied exactly as for a mask tensor.  The
- * result equals steel_attn_fwd / steel_attn_plan given that mask as a
- * [B][Hq][nQB][nKB] tensor; no mask is read.  Every query head shares the
+ * result is that of steel_attn_fwd / steel_attn_plan given that mask as a
+ * [B][Hq][nQB][nKB] tensor, bit for bit unless the lists are split (see
+ * steel_attn_fwd); no mask is read.  Every query head shares the
  * pattern, so head packs always run together.
  *
  *   window_blocks  >= 1 (STEEL_ERR_INVALID_ARGUMENT otherwise)

@@ -38,6 +38,11 @@ struct AttnArgs {
   // and sink blocks of Problem): nothing was indexed, rows and their live lists
   // are computed in the kernel; units: head packs (or heads) per query block
   int coord, win_blocks, sink_blocks, units;
+  // SplitPlan: segments per list, heads per tile, the batch's first unit, its
+  // rows, and its partial results: O [ns][rows][D], then {m, l} [ns][rows]
+  int ns, hp, unit0;
+  long long part_rows, row0;  // row0: the batch's first row
+  float* part;
   int B, Hq, Hkv, S_q, S_k, nQB, nKB, G, causal, delta, R, pack;
   float c;  // scale * log2(e)
 };
@@ -217,6 +222,9 @@ hipError_t launch_attention_ws(const AttnArgs& a, int prec, hipStream_t s);
 // bf16 forms: two waves per head, 64 query rows and half the keys of every
 // tile each (attn_half.hip); pack: heads per item of the list.
 hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, hipStream_t s);
+
+// Combines the partial results of one batch of units (attn_half.hip).
+hipError_t launch_attention_join(const AttnArgs& a, int D, hipStream_t s);
 
 
 }  // namespace steel

@@ -526,8 +526,81 @@ static void launch_one(const AttnArgs& a, int grid, hipStream_t s) {
                        dim3(attn_threads<PACK>()), 0, s, a);
 }
 
+// Workgroups of k_attn_h that the chip holds at one time: per CU two of a head
+// pair at D = 128 and three at D = 64 (registers), four and six of a single head.
+static int half_slots(int D, int heads) { return 256 * (heads == 1 ? (D == 128 ? 4 : 6) : (D == 128 ? 2 : 3)); }
+
+SplitPlan plan_split(const Problem& p) {
+  SplitPlan sp{1, 1, 0, 0};
+  if (!p.coord || p.fp8) return sp;
+  if (p.nQB == 1)  // as many heads of a group as the 64 rows of a tile hold
+    for (int h = p.G; h > 1; --h)
+      if (p.G % h == 0 && (long long)h * p.S_q <= kBlk) {
+        sp.hp = h;
+        break;
+      }
+  const int heads = sp.hp > 1 ? sp.hp : p.pack;  // of a unit
+  sp.units = p.B * (p.Hq / heads);
+  const bool pair = sp.hp == 1 && p.pack > 1;
+  const long long wgs = (long long)sp.units * p.nQB * (pair ? p.pack / 2 : 1);
+  const int slots = half_slots(p.D, pair ? 2 : 1);
+  // Segments of at least 8 tiles (a segment also pays for its Q, its first
+  // tile's latency and its partial result, a few tiles' time; decoding 4
+  // sequences of 8000 keys takes 35.5 us with them, 41.3 with 4 tiles, 36.5
+  // with 16, and 140 unsplit with one head per tile).  One workgroup per CU is
+  // enough: 1000 queries against 11000 keys (256 workgroups) run 227 us whole
+  // and 244 in halves.  Lists of less than 16 tiles stay whole.
+  if (4 * wgs <= slots && p.nKB >= 16) {
+    const long long live = p.win_blocks > 0 ? (long long)p.win_blocks + p.sink_blocks : p.nKB;
+    const long long most = (live < p.nKB ? live : p.nKB) / 8;
+    long long ns = slots / wgs;
+    if (ns > most) ns = most;
+    if (ns > 64) ns = 64;
+    // a unit's partial results fit the fixed array of steel_attn_fwd_noalloc,
+    // which splits as the other calls do
+    const size_t seg_bytes = (size_t)heads * p.S_q * (p.D + 2) * sizeof(float);
+    if (ns > (long long)(kNoAllocBytes / seg_bytes)) ns = (long long)(kNoAllocBytes / seg_bytes);
+    if (ns > 1) {
+      sp.ns = (int)ns;
+      sp.unit_bytes = ns * seg_bytes;
+    }
+  }
+  return sp;
+}
+
+// The bf16 form split over segments and heads per tile, in batches of units
+// whose partial results fit the scratch.
+template <int D>
+static hipError_t launch_split(const Problem& p, AttnArgs a, const SplitPlan& sp, float* part,
+                               size_t part_bytes, hipStream_t s) {
+  const int heads = sp.hp > 1 ? sp.hp : p.pack;
+  const int pack = sp.hp > 1 ? 1 : p.pack;
+  int batch = sp.units;
+  if (sp.ns > 1 && (size_t)batch * sp.unit_bytes > part_bytes) batch = (int)(part_bytes / sp.unit_bytes);
+  if (batch < 1) return hipErrorInvalidValue;
+  a.ns = sp.ns;
+  a.hp = sp.hp;
+  a.part = part;
+  for (int u = 0; u < sp.units; u += batch) {
+    a.unit0 = u;
+    a.units = sp.units - u < batch ? sp.units - u : batch;
+    a.part_rows = (long long)a.units * heads * p.S_q;
+    a.row0 = (long long)u * heads * p.S_q;
+    const int items = a.units * p.nQB;
+    hipError_t e = launch_attention_half(a, D, pack, pack == 1 ? (items + 7) / 8 * 8 : items, s);
+    if (e == hipSuccess && sp.ns > 1) e = launch_attention_join(a, D, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <int D, int PREC>
-static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, hipStream_t s) {
+static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, float* part,
+                           size_t part_bytes, hipStream_t s) {
+  if constexpr (PREC == kBf16) {
+    const SplitPlan sp = plan_split(p);
+    if (sp.ns > 1 || sp.hp > 1) return launch_split<D>(p, a, sp, part, part_bytes, s);
+  }
   if (p.pack > 1) {
     AttnArgs ap = a;
     ap.order = w.order_p;
@@ -562,8 +635,10 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
 
 hipError_t launch_attention(const Problem& p, const void* q, const void* k, const void* v,
                             float* out, float* lse, float scale, const IndexBuffers& w,
-                            const Fp8Buffers& f, hipStream_t s) {
-  AttnArgs a;
+                            const Fp8Buffers& f, float* part, size_t part_bytes, hipStream_t s) {
+  AttnArgs a{};
+  a.ns = 1;
+  a.hp = 1;
   a.q = (const __bf16*)q;
   a.k = (const __bf16*)k;
   a.v = (const __bf16*)v;
@@ -596,9 +671,9 @@ hipError_t launch_attention(const Problem& p, const void* q, const void* k, cons
   a.causal = p.causal;
   a.delta = p.delta;
   a.c = scale * 1.4426950408889634f;
-  if (p.fp8 == kFp8All) return p.D == 64 ? launch_d<64, kFp8All>(p, a, w, s) : launch_d<128, kFp8All>(p, a, w, s);
-  if (p.fp8 == kFp8Pv) return p.D == 64 ? launch_d<64, kFp8Pv>(p, a, w, s) : launch_d<128, kFp8Pv>(p, a, w, s);
-  return p.D == 64 ? launch_d<64, kBf16>(p, a, w, s) : launch_d<128, kBf16>(p, a, w, s);
+  if (p.fp8 == kFp8All) return p.D == 64 ? launch_d<64, kFp8All>(p, a, w, part, part_bytes, s) : launch_d<128, kFp8All>(p, a, w, part, part_bytes, s);
+  if (p.fp8 == kFp8Pv) return p.D == 64 ? launch_d<64, kFp8Pv>(p, a, w, part, part_bytes, s) : launch_d<128, kFp8Pv>(p, a, w, part, part_bytes, s);
+  return p.D == 64 ? launch_d<64, kBf16>(p, a, w, part, part_bytes, s) : launch_d<128, kBf16>(p, a, w, part, part_bytes, s);
 }
 
 }  // namespace steel

@@ -146,7 +146,7 @@ __device__ __forceinline__ void add_rows(const bf16x8 (&pa)[2][2], float (&l)[2]
 template <int D>
 __device__ __forceinline__ void merge_rows(const AttnArgs& a, f32x16 (&o)[2][D / 32], const float (&m)[2],
                                            const float (&l)[2], char* smem, int wave, int kh, int lane,
-                                           int b, int head, int qb) {
+                                           size_t bh, int row0, int nrows, int seg) {
   constexpr int DT = D / 32, HD = DT / 2;
   constexpr int REC = (4 + 2 * 16 * HD) * 256;
   const int n = lane & 31, hf = lane >> 5;
@@ -178,9 +178,30 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, f32x16 (&o)[2][D /
     const float wp = __builtin_amdgcn_exp2f(mp - M);
     const float ls = w * lt[nt] + wp * ltp;
     const float inv = ls > 0.f ? 1.f / ls : 0.f;
-    const int qrow = qb * kBlk + 32 * nt + n;
-    if (qrow < a.S_q) {
-      const size_t row = ((size_t)b * a.Hq + head) * a.S_q + qrow;
+    const int qrow = row0 + 32 * nt + n;
+    if (a.ns > 1) {  // one segment's share: unnormalised, for k_attn_join
+      if (qrow < nrows) {
+        const size_t row = (size_t)seg * a.part_rows + (bh * a.S_q + qrow - (size_t)a.row0);
+        float* ml = a.part + (size_t)a.ns * a.part_rows * D + 2 * row;
+        if (hf == 0 && kh == 0) {
+          ml[0] = M;
+          ml[1] = ls;
+        }
+#pragma unroll
+        for (int j = 0; j < HD; ++j) {
+          const f32x16 lo = o[nt][j], hi = o[nt][HD + j];
+#pragma unroll
+          for (int gq = 0; gq < 4; ++gq) {
+            const f32x4 po = *(const f32x4*)(part + (1 + (nt * HD + j) * 4 + gq) * 256);
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = w * (kh ? hi[4 * gq + e] : lo[4 * gq + e]) + wp * po[e];
+            *(f32x4*)(a.part + row * D + 32 * (kh * HD + j) + 4 * hf + 8 * gq) = v;
+          }
+        }
+      }
+    } else if (qrow < nrows) {
+      const size_t row = bh * a.S_q + qrow;
       // log sum_j exp(scale s_ij) = (M + log2 l) ln 2 (Algorithm 1's statistics)
       if (a.lse != nullptr && hf == 0 && kh == 0)
         a.lse[row] = ls > 0.f ? (M + log2f(ls)) * 0.69314718055994531f : -INFINITY;
@@ -231,13 +252,19 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
 
   // ---- work item: the item of the list, and the head group within it ----
-  const int pk = PACK == 1 ? 1 : a.pack, split = pk / PACK;
+  const int hp = PACK == 1 ? a.hp : 1;  // heads in the rows of a tile
+  const int pk = PACK == 1 ? hp : a.pack, split = PACK == 1 ? 1 : pk / PACK;
   const int x = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
-  const int sub = j % split;
+  int sub = j % split, seg = 0;
   int item;
   if (a.coord) {
-    item = coord_item(a, x, j / split);
+    // segment by segment, so that the workgroups of one run together
+    const int per = (a.units * a.nQB + 7) / 8 * split;  // workgroups of an XCD and segment, at most
+    seg = a.ns > 1 ? j / per : 0;
+    item = seg < a.ns ? coord_item(a, x, (j - seg * per) / split) : -1;
     if (item < 0) return;
+    sub = (j - seg * per) % split;
+    item += a.unit0 * a.nQB;
   } else if (PACK == 1 && a.bucket != nullptr) {
     const cint_p bk = (cint_p)a.bucket;
     const int lo_b = bk[x], hi_b = bk[x + 1];
@@ -257,8 +284,12 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   const int b = bh0 / a.Hq;
   const int h0 = bh0 % a.Hq;
   const int g = h0 / a.G;
-  const LiveRow lr = live_row(a, bh0 * a.nQB + qb, qb);
-  const int L = lr.L;
+  LiveRow lr = live_row(a, bh0 * a.nQB + qb, qb);
+  int L = lr.L, p0 = 0;  // list positions p0 .. p0 + L - 1 are this workgroup's
+  if (a.ns > 1) {
+    p0 = (int)((long long)L * seg / a.ns);
+    L = (int)((long long)L * (seg + 1) / a.ns) - p0;
+  }
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -305,7 +336,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
     }
   };
   // ---- live list: 64 entries in a VGPR ----
-  uint32_t win = lane < L ? live_entry(a, lr, qb, lane) : 0u;
+  uint32_t win = lane < L ? live_entry(a, lr, qb, p0 + lane) : 0u;
   asm volatile("" ::"v"(win));
   uint32_t cw = (uint32_t)__builtin_amdgcn_readlane((int)win, 0), nw = 0;
 
@@ -317,7 +348,9 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   bf16x8 qf[2][KS];
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt) {
-    const int row = min(qb * kBlk + 32 * nt + n, a.S_q - 1);
+    // with hp heads in a tile its rows are consecutive rows of q; rows past the
+    // end read the last one
+    const size_t row = hp > 1 ? (size_t)min(32 * nt + n, hp * a.S_q - 1) : (size_t)min(qb * kBlk + 32 * nt + n, a.S_q - 1);
     const __bf16* qr = a.q + (((size_t)b * a.Hq + head) * a.S_q + row) * D + 8 * hf;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[nt][ks] = *(const bf16x8*)(qr + 16 * ks);
@@ -364,7 +397,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
       const int in = more ? i + 1 : i;
       if ((in & 63) == 0) {
         const int ln = opaque_lane();
-        win = in + ln < L ? live_entry(a, lr, qb, in + ln) : 0u;
+        win = in + ln < L ? live_entry(a, lr, qb, p0 + in + ln) : 0u;
         asm volatile("" ::"v"(win));
       }
       nw = (uint32_t)__builtin_amdgcn_readlane((int)win, in & 63);
@@ -409,7 +442,9 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
         const int kb = (int)(cw & 0x7fffffffu), ln = opaque_lane();
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-          const int lim_abs = min(a.causal ? qb * kBlk + 32 * nt + (ln & 31) + a.delta : INT_MAX - kBlk, a.S_k - 1);
+          int row = 32 * nt + (ln & 31);
+          row = hp > 1 ? row % a.S_q : qb * kBlk + row;
+          const int lim_abs = min(a.causal ? row + a.delta : INT_MAX - kBlk, a.S_k - 1);
           int lim = lim_abs - (kb * kBlk + 32 * kh + 4 * (ln >> 5));
           asm volatile("" : "+v"(lim));  // one threshold per row, compared with constants
 #pragma unroll
@@ -473,7 +508,41 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
     }
   }
 
-  merge_rows<D>(a, o, m, l, smem, wave, kh, lane, b, head, qb);
+  merge_rows<D>(a, o, m, l, smem, wave, kh, lane, (size_t)b * a.Hq + head, hp > 1 ? 0 : qb * kBlk,
+                hp * a.S_q, seg);
+}
+
+// Combines the segments of split lists: with M = max m_s over the segments and
+// w_s = 2^(m_s - M), O = sum w_s O_s / sum w_s l_s.  One thread per row and 4
+// columns, the loads of 8 segments in flight; the parts are read once (2 MB
+// for 128 rows of 32 segments: latency, ~4 us).
+template <int D>
+__global__ __launch_bounds__(256) void k_attn_join(AttnArgs a) {
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  const long long r = idx / (D / 4);
+  if (r >= a.part_rows) return;
+  const int c = (int)(idx - r * (D / 4)) * 4;
+  const float* ml = a.part + (size_t)a.ns * a.part_rows * D;
+  float M = -FLT_MAX;
+  for (int s = 0; s < a.ns; ++s) M = fmaxf(M, ml[2 * ((size_t)s * a.part_rows + r)]);
+  float ls = 0.f;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int s = 0; s < a.ns; ++s) {
+    const size_t row = (size_t)s * a.part_rows + r;
+    const float w = __builtin_amdgcn_exp2f(ml[2 * row] - M);
+    ls += w * ml[2 * row + 1];
+    v += w * *(const f32x4*)(a.part + row * D + c);
+  }
+  const float inv = ls > 0.f ? 1.f / ls : 0.f;
+  const size_t row = (size_t)a.row0 + r;
+  if (a.lse != nullptr && c == 0)
+    a.lse[row] = ls > 0.f ? (M + log2f(ls)) * 0.69314718055994531f : -INFINITY;
+  if (a.out_bf16)
+    *(bf16x4*)((__bf16*)a.out + row * D + c) =
+        bf16x4{(__bf16)(v[0] * inv), (__bf16)(v[1] * inv), (__bf16)(v[2] * inv), (__bf16)(v[3] * inv)};
+  else
+    *(f32x4*)(a.out + row * D + c) = v * inv;
 }
 
 template <int D, int PACK, int ST, int WPE>
@@ -487,13 +556,21 @@ static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
 hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, hipStream_t s) {
   if (items <= 0) return hipSuccess;
   if (pack == 1) {
+    items = a.coord ? items * a.ns : items;
     if (D == 64) launch_h<64, 1, 1, 3>(a, items, s);
     else launch_h<128, 1, 1, 2>(a, items, s);
   } else {
-    const int grid = xcd_grid(items) * (pack / 2);
+    const int grid = (a.coord ? (items + 7) / 8 * 8 * a.ns : xcd_grid(items)) * (pack / 2);
     if (D == 64) launch_h<64, 2, 2, 3>(a, grid, s);
     else launch_h<128, 2, 2, 2>(a, grid, s);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_attention_join(const AttnArgs& a, int D, hipStream_t s) {
+  const dim3 grid((unsigned)((a.part_rows * (D / 4) + 255) / 256));
+  if (D == 64) hipLaunchKernelGGL(k_attn_join<64>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_attn_join<128>, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

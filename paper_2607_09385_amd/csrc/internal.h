@@ -151,6 +151,20 @@ constexpr int kHeaderInts = kPackItems + 1;
 constexpr int kDemotePacks = 64;
 constexpr int kDemoteMinSingle = 1024;
 
+// Calls without a mask tensor whose query blocks are too few to fill the chip
+// (decoding, short chunks of queries against a long key cache), bf16 only:
+// every live list is cut into ns segments, each run by a workgroup of its own
+// that leaves its partial (m, l, O) in scratch, and k_attn_join combines them.
+// With a single query block the hp query heads of a group whose rows fit one
+// 64-row tile together are run as one item (hp = 1: one head per tile).
+struct SplitPlan {
+  int ns;             // segments per list (1: not split)
+  int hp;             // query heads packed into one tile's rows
+  size_t unit_bytes;  // scratch per unit (hp heads, or the heads of a pack) when ns > 1
+  int units;
+};
+SplitPlan plan_split(const Problem& p);
+
 // Up to this many head packs of 4 at D = 128 (bf16) are run two heads to a
 // workgroup instead of four: a persistent workgroup per CU leaves CUs idle.
 constexpr int kFewPacks = 256;
@@ -193,9 +207,11 @@ hipError_t launch_fp8_prepass(const Problem& p, const void* k, const void* v, co
 // Enqueue the fused attention over both item lists; lse (nullable) receives
 // the row log-sum-exp [B][Hq][S_q].  f: the fp8 operands when p.fp8, else
 // ignored.
+// part: scratch for the partial results of plan_split (at least one unit's; the
+// units are taken in as many batches as it needs), or nullptr when ns == 1.
 hipError_t launch_attention(const Problem& p, const void* q, const void* k, const void* v,
                             float* out, float* lse, float scale, const IndexBuffers& w,
-                            const Fp8Buffers& f, hipStream_t stream);
+                            const Fp8Buffers& f, float* part, size_t part_bytes, hipStream_t stream);
 
 // Enqueue the merge of n_parts partial results over disjoint key sets
 // (attn_merge.hip): o_parts [n_parts][rows][D], lse_parts [n_parts][rows].

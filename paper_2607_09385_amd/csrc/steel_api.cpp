@@ -291,9 +291,11 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
                const uint8_t* block_mask, void* out, float* lse, float scale, void* stream) {
   int rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p.coord && !p.fp8) {  // no index, no operands: nothing to keep
-    const hipError_t e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale,
-                                                 steel::IndexBuffers{}, steel::Fp8Buffers{}, s);
+  const steel::SplitPlan sp = steel::plan_split(p);
+  if (p.coord && !p.fp8 && sp.ns == 1) {  // no index, operands or partial results: nothing to keep
+    const hipError_t e =
+        steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale,
+                                steel::IndexBuffers{}, steel::Fp8Buffers{}, nullptr, 0, s);
     return e == hipSuccess ? STEEL_OK : hip_fail(e, "launching kernels");
   }
   int dev = 0;
@@ -302,7 +304,8 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
   std::unique_lock<std::mutex> lk;
   StreamScratch* slot = nullptr;
   char* ws = nullptr;
-  if ((rc = scratch_begin(dev, s, L.total, &lk, &slot, &ws)) != STEEL_OK) return rc;
+  const size_t part = sp.unit_bytes * (size_t)sp.units;  // partial results of split lists
+  if ((rc = scratch_begin(dev, s, align256(L.total) + part, &lk, &slot, &ws)) != STEEL_OK) return rc;
   const steel::IndexBuffers w = p.coord ? steel::IndexBuffers{} : carve(ws, L);
   steel::Fp8Buffers f{};
   if (p.fp8) {
@@ -314,7 +317,8 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
   hipError_t e = p.coord ? hipSuccess : steel::launch_block_index(p, block_mask, w, s);
   if (e == hipSuccess && p.fp8) e = steel::launch_fp8_prepass(p, k, v, f, s);
   if (e == hipSuccess)
-    e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale, w, f, s);
+    e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale, w, f,
+                                reinterpret_cast<float*>(ws + align256(L.total)), part, s);
   const int re = scratch_end(slot, dev, s);
   if (e != hipSuccess) return hip_fail(e, "launching kernels");
   return re;
@@ -402,7 +406,7 @@ int steel_attn_fwd_noalloc(const void* q, const void* k, const void* v,
   e = p.coord ? hipSuccess : steel::launch_block_index(p, block_mask, w, s);
   if (e == hipSuccess)
     e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), nullptr, scale, w,
-                                steel::Fp8Buffers{}, s);
+                                steel::Fp8Buffers{}, reinterpret_cast<float*>(ws), steel::kNoAllocBytes, s);
   if (e != hipSuccess) return hip_fail(e, "launching kernels");
   return STEEL_OK;
 }
@@ -480,7 +484,7 @@ int steel_attn_run(const void* q, const void* k, const void* v, void* out, int B
   hipError_t e = steel::launch_attention(
       p, q, k, v, static_cast<float*>(out), nullptr, scale,
       carve(const_cast<char*>(static_cast<const char*>(workspace)), L), steel::Fp8Buffers{},
-      static_cast<hipStream_t>(stream));
+      nullptr, 0, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "launching the attention kernels");
   return STEEL_OK;
 }

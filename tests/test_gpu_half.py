@@ -79,12 +79,13 @@ def test_growing_maxima(D, Hq, Hkv):
     (1, 8, 8, 512, 512, 64, True, 2, 1),
     (1, 3, 3, 513, 700, 64, True, 3, 0),
     (2, 8, 2, 700, 513, 128, False, 1, 2),
-    (1, 12, 3, 1000, 1000, 64, True, 5, 100),
-    (1, 4, 2, 320, 1280, 128, True, 1000, 0),
+    (1, 12, 3, 950, 950, 64, True, 5, 100),
+    (1, 4, 2, 320, 900, 128, True, 1000, 0),
     (9, 16, 4, 640, 640, 128, True, 2, 1),
     (1, 2, 2, 900, 100, 128, True, 2, 1),
 ], ids=lambda c: "x".join(str(int(v)) for v in c))
 def test_coordinates_equal_mask_tensor(shape):
+    """Bit for bit where the lists are not split (fewer than 16 key blocks)."""
     B, Hq, Hkv, S_q, S_k, D, causal, win, sink = shape
     q, k, v = (t.cuda() for t in small_qkv(7, B, Hq, Hkv, S_q, S_k, D))
     nQB, nKB = -(-S_q // 64), -(-S_k // 64)
@@ -100,3 +101,56 @@ def test_coordinates_equal_mask_tensor(shape):
         a = s.attn_fwd_lse(q, k, v, None, causal=causal, causal_offset=37, fp8=fp8)
         b = s.attn_fwd_lse(q, k, v, torch.ones_like(m), causal=causal, causal_offset=37, fp8=fp8)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+SPLIT = [
+    # B, Hq, Hkv, S_q, S_k, D, causal: few query blocks, long key lists
+    (1, 4, 1, 1, 2048, 128, True),
+    (3, 8, 2, 1, 1111, 64, True),
+    (2, 8, 1, 8, 1024, 128, True),     # 8 heads x 8 rows fill a tile
+    (1, 8, 1, 9, 1500, 64, False),     # 4 heads x 9 rows
+    (1, 6, 2, 21, 1024, 128, True),    # 3 heads x 21 rows
+    (1, 5, 5, 64, 2000, 64, True),     # one head per tile
+    (1, 8, 4, 65, 1090, 128, True),    # two query blocks, packs of 2
+    (1, 4, 1, 200, 3000, 128, True),
+    (1, 2, 2, 300, 1024, 64, False),
+    (1, 1, 1, 1100, 1030, 128, True),  # dead rows at the start
+]
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=lambda c: "x".join(str(int(v)) for v in c))
+def test_split_lists(case):
+    """Lists cut into segments and several heads in one tile's rows: output
+    and log-sum-exp against the oracle, and the other forms of the call, which
+    split alike, bit for bit."""
+    B, Hq, Hkv, S_q, S_k, D, causal = case
+    q, k, v = small_qkv(13, B, Hq, Hkv, S_q, S_k, D)
+    qc, kc, vc = q.cuda(), k.cuda(), v.cuda()
+    want, want_lse = oracle.attention_lse(q, k, v, None, D ** -0.5, causal, 64, S_k - S_q)
+    s = steel()
+    out = torch.full((B, Hq, S_q, D), float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.full((B, Hq, S_q), float("nan"), dtype=torch.float32, device="cuda")
+    s.attn_fwd_lse(qc, kc, vc, scale=D ** -0.5, causal=causal, out=out, lse=lse)
+    check(out, want, str(case))
+    got = lse.double().cpu().numpy()
+    dead = np.isneginf(want_lse)
+    assert np.array_equal(np.isneginf(got), dead)
+    assert np.abs(got[~dead] - want_lse[~dead]).max(initial=0.0) <= 1e-3
+    assert torch.equal(out, s.attn_fwd(qc, kc, vc, scale=D ** -0.5, causal=causal))
+    bf, _ = s.attn_fwd_lse(qc, kc, vc, scale=D ** -0.5, causal=causal, out_dtype=torch.bfloat16)
+    assert torch.equal(bf, out.to(torch.bfloat16))
+    other = torch.full_like(out, float("nan"))
+    st = s._lib.load().steel_attn_fwd_noalloc(
+        qc.data_ptr(), kc.data_ptr(), vc.data_ptr(), None, other.data_ptr(), B, Hq, Hkv, S_q, S_k,
+        D, 64, D ** -0.5, int(causal), torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    assert torch.equal(out, other)
+
+
+def test_split_window():
+    q, k, v = (t.cuda() for t in small_qkv(17, 1, 4, 1, 640, 8192, 64))
+    qb, kb = np.arange(10)[:, None], np.arange(128)[None, :]
+    m = (((kb <= qb) & (kb > qb - 2)) | (kb < 70)).astype(np.uint8)
+    m = np.ascontiguousarray(np.broadcast_to(m, (1, 4, 10, 128)))
+    got = steel().attn_fwd_window(q, k, v, 2, 70, causal=False)
+    check(got, oracle.attention(q.cpu(), k.cpu(), v.cpu(), m, 64 ** -0.5, False, 64), "window")
