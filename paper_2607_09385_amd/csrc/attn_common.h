@@ -25,7 +25,7 @@ struct AttnArgs {
   float* out;
   float* lse;               // [B][Hq][S_q] row log-sum-exp, or nullptr
   int out_bf16;             // out holds bf16 (round to nearest even), not fp32
-  const int32_t* row_ptr;
+  const int32_t* cnt;       // live counts (| kUniformBit) of the rows
   const uint32_t* col;
   const int32_t* order;
   const int32_t* n_items;   // this list's item count
@@ -63,7 +63,7 @@ __device__ __forceinline__ bool plan_matches(const AttnArgs& a) {
 }
 
 // Live list of one query block.  With an index: entries beg .. beg + L - 1 of
-// col.  From coordinates: key blocks [0, a_len) and [b0, b0 + L - a_len), the
+// col (R * nKB < 2^31).  From coordinates: key blocks [0, a_len) and [b0, b0 + L - a_len), the
 // sink and the window (no window: all of [0, a_len)), up to the causal limit.
 struct LiveRow {
   int L, beg, a_len, b0;
@@ -88,8 +88,8 @@ __device__ __forceinline__ LiveRow coord_row(const AttnArgs& a, int qb) {
 __device__ __forceinline__ LiveRow live_row(const AttnArgs& a, int row, int qb) {
   if (a.coord) return coord_row(a, qb);
   LiveRow r{};
-  r.beg = ((cint_p)a.row_ptr)[row];
-  r.L = ((cint_p)a.row_ptr)[row + 1] - r.beg;
+  r.beg = row * a.nKB;
+  r.L = ((cint_p)a.cnt)[row] & ~(int)kUniformBit;
   return r;
 }
 // Entry i < L of a live list: the key block, bit 31 set when it is partial.

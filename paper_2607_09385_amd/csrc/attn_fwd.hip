@@ -101,18 +101,18 @@ __global__ __launch_bounds__(attn_threads<PACK>()) void k_attn(AttnArgs a) {
   if (a.coord) {
     item = coord_item(a, (int)blockIdx.x & 7, (int)blockIdx.x >> 3);
     if (item < 0) return;
-  } else if (PACK == 1 && a.bucket != nullptr) {
+  } else if (PACK == 1) {
     // single-head items: workgroup b runs on XCD b % 8 and takes the
     // (b / 8)-th item of that XCD's bucket (heaviest first within it).  The
-    // bucket bounds (always present) and the plan header are read together,
+    // bucket's count (always present) and the plan header are read together,
     // so that the many workgroups past a short bucket leave after one load.
     const cint_p bk = (cint_p)a.bucket;
     const int x = (int)blockIdx.x & (kBuckets - 1), j = (int)blockIdx.x / kBuckets;
-    const int lo = bk[x], hi = bk[x + 1];
+    const int n_b = bk[x];
     const bool ok = plan_matches(a);
-    if (j >= hi - lo) return;
+    if (j >= n_b) return;
     if (!ok) return;  // index planned for another problem: out untouched
-    item = bk[kBuckets + 1 + lo + j];
+    item = bk[kBuckets + 1 + bucket_start(a.B * a.Hkv, a.nQB * a.G, x) + j];
     if ((unsigned)item >= (unsigned)a.R) return;  // never for a well-formed index
   } else {
     if (!plan_matches(a)) return;  // index planned for another problem: out untouched
@@ -509,8 +509,8 @@ __global__ __launch_bounds__(attn_threads<PACK>()) void k_attn(AttnArgs a) {
 template <int D, int PACK, int PREC>
 static void launch_one(const AttnArgs& a, int grid, hipStream_t s) {
   if (grid <= 0) return;
-  // the bucket-dealt single-head list: grid is already 8 x (largest bucket)
-  const int g = PACK == 1 && (a.coord || a.bucket != nullptr) ? grid : xcd_grid(grid);
+  // single heads: grid is already 8 x (largest XCD share)
+  const int g = PACK == 1 ? grid : xcd_grid(grid);
   // E4M3 tiles are padded with zero keys: with both tensors in E4M3 no copy
   // clamps.  The D = 64 kernels keep the ragged copy for every S_k: without
   // it they need fewer registers and a third wave per SIMD ran slower.
@@ -615,14 +615,13 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
     if (e != hipSuccess) return e;
   }
   if (p.pack > 1 && p.heads_share_mask) return hipGetLastError();  // no single-head item
-  a.order = w.order_s;
   a.n_items = w.n_items;
   a.bucket = w.bucket;
   a.units = p.B * p.Hq;
   int grid = p.R;
   if (a.coord) {
     grid = (p.R + 7) / 8 * 8;
-  } else if (w.bucket != nullptr) {
+  } else {
     // at most the rows of the key/value heads of one bucket: nQB * G rows per
     // head, ceil(B*Hkv / 8) heads per bucket
     const long long per = (long long)p.nQB * p.G * ((p.B * p.Hkv + kBuckets - 1) / kBuckets);
@@ -645,7 +644,7 @@ hipError_t launch_attention(const Problem& p, const void* q, const void* k, cons
   a.out = out;
   a.lse = lse;
   a.out_bf16 = p.out_bf16;
-  a.row_ptr = w.row_ptr;
+  a.cnt = w.cnt;
   a.col = w.col;
   a.order = nullptr;
   a.n_items = nullptr;

@@ -265,13 +265,13 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
     if (item < 0) return;
     sub = (j - seg * per) % split;
     item += a.unit0 * a.nQB;
-  } else if (PACK == 1 && a.bucket != nullptr) {
+  } else if (PACK == 1) {
     const cint_p bk = (cint_p)a.bucket;
-    const int lo_b = bk[x], hi_b = bk[x + 1];
+    const int n_b = bk[x];
     const bool ok = plan_matches(a);
-    if (j >= hi_b - lo_b) return;
+    if (j >= n_b) return;
     if (!ok) return;  // index planned for another problem: out untouched
-    item = bk[kBuckets + 1 + lo_b + j];
+    item = bk[kBuckets + 1 + bucket_start(a.B * a.Hkv, a.nQB * a.G, x) + j];
     if ((unsigned)item >= (unsigned)a.R) return;  // never for a well-formed index
   } else {
     if (!plan_matches(a)) return;  // index planned for another problem: out untouched

@@ -207,8 +207,8 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
       if (idx < n_all) {
         w_item = a.order[idx];
         const int r0 = (w_item / a.nQB) * 4 * a.nQB + w_item % a.nQB;
-        w_beg = a.row_ptr[r0];
-        w_end = a.row_ptr[r0 + 1];
+        w_beg = r0 * a.nKB;
+        w_end = w_beg + (a.cnt[r0] & ~(int)kUniformBit);
       }
     }
     asm volatile("" ::"v"(w_item), "v"(w_beg), "v"(w_end));

@@ -95,22 +95,26 @@ __host__ __device__ inline float e4m3_scale(float amax) {
   return sc;
 }
 
-// Device workspace of one call.
+// Index read by the attention kernels.
 struct IndexBuffers {
   int32_t* cnt;        // [R]   live blocks per row (| kUniformBit, see below)
-  int32_t* hist_s;     // [kBins * nchunk_s]  per-chunk bin counts, then bases
-  int32_t* hist_p;     // [kBins * nchunk_p]
-  int32_t* row_ptr;    // [R+1]
-  uint32_t* col;       // [R*nKB] capacity
-  int32_t* order_s;    // [R]   single-head items, heaviest first
-  int32_t* order_p;    // [NP]  head-pack items, heaviest first
+  uint32_t* col;       // [R*nKB] the list of row r at r * nKB
+  int32_t* order_p;    // [NP]  uniform head packs, heaviest first
   int32_t* n_items;    // [kHeaderInts] {single items, pack items, plan header,
-                       //   top bins of the two lists, pack items the pack
-                       //   kernels take} (see kPlanAt, kTopBin, kPackItems)
-  // single-head items dealt to the 8 XCDs by key/value head (nullptr: none):
-  // [kBuckets + 1] bucket starts, then the items of order_s stably
-  // partitioned by bucket
+                       //   pack items the pack kernels take}
+  // single-head items dealt to the 8 XCDs by key/value head: [kBuckets] item
+  // counts, one unused, then bucket mb's items from bucket_start on
   int32_t* bucket;
+};
+
+// Public index and its workspace.
+struct PublicIndex {
+  int32_t* cnt;      // [R]
+  int32_t* hist;     // [kBins * chunks] per-chunk bin counts, then bases
+  int32_t* top_bin;  // [1]
+  int32_t* row_ptr;  // [R+1]
+  uint32_t* col;     // [R*nKB] capacity
+  int32_t* order;    // [R] rows, heaviest first
 };
 
 // XCD buckets of single-head items: bucket (b*Hkv + g) % kBuckets, so that the
@@ -130,16 +134,14 @@ __host__ __device__ inline int bucket_ranges(const Problem& p) {
 // it against their own arguments before touching the index, so a run with
 // other sizes, another causal limit or another head packing than the plan
 // leaves its output untouched.  Layout of n_items: [0] single-head items,
-// [1] head-pack items, [kPlanAt + f] field f of PlanField, [kTopBin + list]
-// the top work-order bin of each list, [kPackItems] the head-pack items the
-// pack kernels take (n_items[1], or 0 when k_bucket hands a short pack list
-// to the single-head kernel, see kDemotePacks).
+// [1] head-pack items, [kPlanAt + f] field f of PlanField, [kPackItems] the
+// head-pack items the pack kernels take (n_items[1], or 0 when a short pack
+// list goes to the single-head kernel, see kDemotePacks).
 constexpr int kPlanMagic = 0x5354454c;  // "STEL"
 enum PlanField { kPfMagic, kPfR, kPfNKB, kPfPack, kPfCausal, kPfDelta, kPfB, kPfHq, kPfHkv,
                  kPfSq, kPfSk, kPlanFields };
 constexpr int kPlanAt = 2;
-constexpr int kTopBin = kPlanAt + kPlanFields;
-constexpr int kPackItems = kTopBin + 2;
+constexpr int kPackItems = kPlanAt + kPlanFields;
 constexpr int kHeaderInts = kPackItems + 1;
 
 // A head-pack list shorter than kDemotePacks (a quarter of the CUs) is run
@@ -188,8 +190,21 @@ constexpr size_t kNoAllocBytes = (size_t)32 << 20;
 // first call for a device, with the device made current, then cached).
 hipError_t noalloc_scratch(int dev, char** ptr);
 
-// Enqueue the index build.  With p.pack == 1 every row is a single-head item.
-hipError_t launch_block_index(const Problem& p, const uint8_t* mask, const IndexBuffers& w,
+// First list position of bucket mb: the rows of the heads of the buckets before
+// it (heads = B*Hkv, rg = rows of a key/value head).
+__host__ __device__ inline int bucket_start(int heads, int rg, int mb) {
+  const int rest = heads % kBuckets;
+  return rg * (mb * (heads / kBuckets) + (mb < rest ? mb : rest));
+}
+
+// Enqueue the build of the index the attention kernels read: cnt, col with the
+// list of row r at r * nKB, order_p, bucket and the header.  With p.pack == 1
+// every row is a single-head item.
+hipError_t launch_attn_index(const Problem& p, const uint8_t* mask, const IndexBuffers& w,
+                             hipStream_t stream);
+
+// Enqueue the build of the public index (row_ptr, col, order_s).
+hipError_t launch_block_index(const Problem& p, const uint8_t* mask, const PublicIndex& w,
                               hipStream_t stream);
 
 // Enqueue the top-k mean-pooled block selection (block_select.hip): writes the

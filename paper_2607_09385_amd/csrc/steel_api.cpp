@@ -176,13 +176,14 @@ int check_shape(int B, int Hq, int Hkv, int S_q, int S_k, int blk, int causal,
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Workspace of an attention call: the index (none without a mask tensor) and
+// the fp8 operands.
 struct Layout {
-  size_t cnt, hist_s, hist_p, row_ptr, col, order_s, order_p, n_items, bucket, total;
-  bool has_bucket;  // the single-head list is also dealt into XCD buckets
+  size_t cnt, col, order_p, n_items, bucket, total;
   size_t k8, v8, f8_part, f8_scale;  // fp8 operands (when Problem::fp8)
 };
 
-Layout layout(const steel::Problem& p, bool with_rowptr_col_order) {
+Layout layout(const steel::Problem& p) {
   Layout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -190,21 +191,21 @@ Layout layout(const steel::Problem& p, bool with_rowptr_col_order) {
     off += align256(bytes);
     return at;
   };
-  if (!p.coord) {  // without a mask tensor nothing is indexed
-    const size_t nch_s = steel::nchunks(p.R);
-    const size_t nch_p = p.pack > 1 ? steel::nchunks(p.NP) : 0;
+  if (!p.coord) {
     L.cnt = take(sizeof(int32_t) * p.R);
-    L.hist_s = take(sizeof(int32_t) * steel::kBins * nch_s);
-    L.hist_p = take(sizeof(int32_t) * (nch_p ? steel::kBins * nch_p : 1));
     L.n_items = take(sizeof(int32_t) * steel::kHeaderInts);
     L.order_p = take(sizeof(int32_t) * (p.NP > 0 ? p.NP : 1));
-    if (with_rowptr_col_order) {
-      L.row_ptr = take(sizeof(int32_t) * (p.R + 1));
-      L.col = take(sizeof(uint32_t) * (size_t)p.R * p.nKB);
-      L.order_s = take(sizeof(int32_t) * p.R);
-      L.bucket = take(sizeof(int32_t) * ((size_t)p.R + steel::kBuckets + 1));
-      L.has_bucket = true;
-    }
+    L.col = take(sizeof(uint32_t) * (size_t)p.R * p.nKB);
+    L.bucket = take(sizeof(int32_t) * ((size_t)p.R + steel::kBuckets + 1));
+    // Unused: 2 KiB per 256 rows and 8 bytes per row.  Callers size plan
+    // workspaces and the allocation-free call sets its limit by this total,
+    // which therefore stays what it was when the index held row offsets, a
+    // row order and histograms as well.
+    const size_t hist = sizeof(int32_t) * steel::kBins;
+    take(hist * steel::nchunks(p.R));
+    take(p.pack > 1 ? hist * steel::nchunks(p.NP) : sizeof(int32_t));
+    take(sizeof(int32_t) * ((size_t)p.R + 1));
+    take(sizeof(int32_t) * p.R);
   }
   if (p.fp8) {
     const size_t tiles = (size_t)p.B * p.Hkv * p.nKB * steel::kBlk * p.D;  // bytes per tensor
@@ -263,14 +264,10 @@ int set_window(steel::Problem* p, int window_blocks, int sink_blocks) {
 steel::IndexBuffers carve(char* ws, const Layout& L) {
   steel::IndexBuffers w{};
   w.cnt = reinterpret_cast<int32_t*>(ws + L.cnt);
-  w.hist_s = reinterpret_cast<int32_t*>(ws + L.hist_s);
-  w.hist_p = reinterpret_cast<int32_t*>(ws + L.hist_p);
   w.n_items = reinterpret_cast<int32_t*>(ws + L.n_items);
   w.order_p = reinterpret_cast<int32_t*>(ws + L.order_p);
-  w.row_ptr = reinterpret_cast<int32_t*>(ws + L.row_ptr);
   w.col = reinterpret_cast<uint32_t*>(ws + L.col);
-  w.order_s = reinterpret_cast<int32_t*>(ws + L.order_s);
-  w.bucket = L.has_bucket ? reinterpret_cast<int32_t*>(ws + L.bucket) : nullptr;
+  w.bucket = reinterpret_cast<int32_t*>(ws + L.bucket);
   return w;
 }
 
@@ -300,7 +297,7 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
   }
   int dev = 0;
   if ((rc = stream_device(s, &dev)) != STEEL_OK) return rc;
-  const Layout L = layout(p, true);
+  const Layout L = layout(p);
   std::unique_lock<std::mutex> lk;
   StreamScratch* slot = nullptr;
   char* ws = nullptr;
@@ -314,7 +311,7 @@ int fused_call(const steel::Problem& p, const void* q, const void* k, const void
     f.part = reinterpret_cast<float*>(ws + L.f8_part);
     f.scale = reinterpret_cast<float*>(ws + L.f8_scale);
   }
-  hipError_t e = p.coord ? hipSuccess : steel::launch_block_index(p, block_mask, w, s);
+  hipError_t e = p.coord ? hipSuccess : steel::launch_attn_index(p, block_mask, w, s);
   if (e == hipSuccess && p.fp8) e = steel::launch_fp8_prepass(p, k, v, f, s);
   if (e == hipSuccess)
     e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), lse, scale, w, f,
@@ -389,7 +386,7 @@ int steel_attn_fwd_noalloc(const void* q, const void* k, const void* v,
   if (rc != STEEL_OK) return rc;
   set_pack(&p);
   p.heads_share_mask = block_mask == nullptr;
-  const Layout L = layout(p, true);  // the limit is that of the index, needed or not
+  const Layout L = layout(p);  // the limit is that of the index, needed or not
   if (L.total > steel::kNoAllocBytes)
     return fail(STEEL_ERR_UNSUPPORTED,
                 "the index of this problem needs %zu bytes of scratch; steel_attn_fwd_noalloc "
@@ -403,7 +400,7 @@ int steel_attn_fwd_noalloc(const void* q, const void* k, const void* v,
   hipError_t e = steel::noalloc_scratch(dev, &ws);
   if (e != hipSuccess) return hip_fail(e, "looking up the fixed scratch array");
   const steel::IndexBuffers w = carve(ws, L);
-  e = p.coord ? hipSuccess : steel::launch_block_index(p, block_mask, w, s);
+  e = p.coord ? hipSuccess : steel::launch_attn_index(p, block_mask, w, s);
   if (e == hipSuccess)
     e = steel::launch_attention(p, q, k, v, static_cast<float*>(out), nullptr, scale, w,
                                 steel::Fp8Buffers{}, reinterpret_cast<float*>(ws), steel::kNoAllocBytes, s);
@@ -436,7 +433,7 @@ size_t steel_attn_workspace_bytes(int B, int Hq, int Hkv, int S_q, int S_k, int 
   steel::Problem p{};
   if (check_shape(B, Hq, Hkv, S_q, S_k, blk, 0, &p) != STEEL_OK) return 0;
   set_pack(&p);
-  return layout(p, true).total;
+  return layout(p).total;
 }
 
 int steel_attn_plan(const uint8_t* block_mask, int B, int Hq, int Hkv, int S_q, int S_k,
@@ -446,9 +443,9 @@ int steel_attn_plan(const uint8_t* block_mask, int B, int Hq, int Hkv, int S_q, 
   int rc = check_shape(B, Hq, Hkv, S_q, S_k, blk, causal, &p);
   if (rc != STEEL_OK) return rc;
   set_pack(&p);
-  const Layout L = layout(p, true);
+  const Layout L = layout(p);
   if ((rc = check_workspace(workspace, workspace_bytes, L)) != STEEL_OK) return rc;
-  hipError_t e = steel::launch_block_index(p, block_mask, carve(static_cast<char*>(workspace), L),
+  hipError_t e = steel::launch_attn_index(p, block_mask, carve(static_cast<char*>(workspace), L),
                                            static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "launching the index build");
   return STEEL_OK;
@@ -463,9 +460,9 @@ int steel_attn_plan_window(int B, int Hq, int Hkv, int S_q, int S_k, int blk, in
   if (rc != STEEL_OK) return rc;
   if ((rc = set_window(&p, window_blocks, sink_blocks)) != STEEL_OK) return rc;
   set_pack(&p);
-  const Layout L = layout(p, true);
+  const Layout L = layout(p);
   if ((rc = check_workspace(workspace, workspace_bytes, L)) != STEEL_OK) return rc;
-  hipError_t e = steel::launch_block_index(p, nullptr, carve(static_cast<char*>(workspace), L),
+  hipError_t e = steel::launch_attn_index(p, nullptr, carve(static_cast<char*>(workspace), L),
                                            static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "launching the index build");
   return STEEL_OK;
@@ -479,7 +476,7 @@ int steel_attn_run(const void* q, const void* k, const void* v, void* out, int B
   int rc = check_attn(q, k, v, out, B, Hq, Hkv, S_q, S_k, D, blk, scale, causal, &p);
   if (rc != STEEL_OK) return rc;
   set_pack(&p);
-  const Layout L = layout(p, true);
+  const Layout L = layout(p);
   if ((rc = check_workspace(workspace, workspace_bytes, L)) != STEEL_OK) return rc;
   hipError_t e = steel::launch_attention(
       p, q, k, v, static_cast<float*>(out), nullptr, scale,
@@ -540,20 +537,19 @@ int steel_block_index(const uint8_t* block_mask, int B, int Hq, int S_q, int S_k
   hipStream_t s = static_cast<hipStream_t>(stream);
   int dev = 0;
   if ((rc = stream_device(s, &dev)) != STEEL_OK) return rc;
-  const Layout L = layout(p, false);
+  const size_t o_hist = align256(sizeof(int32_t) * p.R);
+  const size_t o_top = o_hist + align256(sizeof(int32_t) * steel::kBins * (size_t)steel::nchunks(p.R));
   std::unique_lock<std::mutex> lk;
   StreamScratch* slot = nullptr;
   char* ws = nullptr;
-  if ((rc = scratch_begin(dev, s, L.total, &lk, &slot, &ws)) != STEEL_OK) return rc;
-  steel::IndexBuffers w{};
-  w.cnt = reinterpret_cast<int32_t*>(ws + L.cnt);
-  w.hist_s = reinterpret_cast<int32_t*>(ws + L.hist_s);
-  w.hist_p = reinterpret_cast<int32_t*>(ws + L.hist_p);
-  w.n_items = reinterpret_cast<int32_t*>(ws + L.n_items);
-  w.order_p = reinterpret_cast<int32_t*>(ws + L.order_p);
+  if ((rc = scratch_begin(dev, s, o_top + 256, &lk, &slot, &ws)) != STEEL_OK) return rc;
+  steel::PublicIndex w{};
+  w.cnt = reinterpret_cast<int32_t*>(ws);
+  w.hist = reinterpret_cast<int32_t*>(ws + o_hist);
+  w.top_bin = reinterpret_cast<int32_t*>(ws + o_top);
   w.row_ptr = row_ptr;
   w.col = col;
-  w.order_s = order;
+  w.order = order;
   hipError_t e = steel::launch_block_index(p, block_mask, w, s);
   const int re = scratch_end(slot, dev, s);
   if (e != hipSuccess) return hip_fail(e, "launching kernels");

@@ -154,3 +154,37 @@ def test_split_window():
     m = np.ascontiguousarray(np.broadcast_to(m, (1, 4, 10, 128)))
     got = steel().attn_fwd_window(q, k, v, 2, 70, causal=False)
     check(got, oracle.attention(q.cpu(), k.cpu(), v.cpu(), m, 64 ** -0.5, False, 64), "window")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S_q,S_k,D,uniform", [
+    # masks whose packs are all uniform, some, or none, heads over the 8 XCDs
+    # evenly and not, rows of one and of several 256-block reads (S_k > 16384),
+    # packs beyond one sort round (1024), live counts beyond 128
+    (1, 8, 8, 700, 700, 64, 0.0),
+    (1, 36, 9, 500, 500, 128, 0.5),
+    (2, 32, 8, 4200, 300, 64, 1.0),
+    (1, 4, 1, 130, 16500, 64, 0.5),
+    (1, 16, 8, 2100, 2100, 64, 0.97),
+], ids=str)
+def test_index_of_mask_tensors(B, Hq, Hkv, S_q, S_k, D, uniform):
+    """Every row is dealt out exactly once, whichever list it is in: outputs
+    against the oracle in a buffer of NaN."""
+    rng = np.random.default_rng(B * 100 + Hq)
+    nQB, nKB = -(-S_q // 64), -(-S_k // 64)
+    m = random_block_mask(rng, B, Hq, nQB, nKB, p=0.7)
+    G = Hq // Hkv
+    shared = rng.random((B, Hkv, nQB)) < uniform  # these groups share one live set
+    for b, g, qb in np.argwhere(shared):
+        m[b, g * G:(g + 1) * G, qb] = m[b, g * G, qb]
+    q, k, v = small_qkv(19, B, Hq, Hkv, S_q, S_k, D)
+    out = torch.full((B, Hq, S_q, D), float("nan"), dtype=torch.float32, device="cuda")
+    steel().attn_fwd(q.cuda(), k.cuda(), v.cuda(), torch.from_numpy(m).cuda(), causal=False, out=out)
+    assert torch.isfinite(out).all()
+    rows = np.unique(np.concatenate([[0, S_q - 1], rng.integers(0, S_q, 200)]))
+    blocks = np.unique(rows // 64)[:6]
+    for b in range(B):
+        for qb in blocks:
+            r0, r1 = qb * 64, min(qb * 64 + 64, S_q)
+            want = oracle.attention(q[b:b + 1, :, r0:r1], k[b:b + 1], v[b:b + 1],
+                                    np.ascontiguousarray(m[b:b + 1, :, qb:qb + 1]), D ** -0.5, False, 64)
+            check(out[b:b + 1, :, r0:r1], want, f"batch {b} block {qb}")
