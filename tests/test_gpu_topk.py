@@ -119,3 +119,31 @@ def test_topk_mask_ties(kind, causal):
         want = oracle.topk_meanpool_mask(q, k, 1, 10, causal)
         got = got.cpu().numpy()
         assert np.array_equal(got, want), f"{int((got != want).sum())} mask bytes differ"
+
+
+@pytest.mark.parametrize("S_q,nKB,causal,keep", [
+    (64, 1, False, (1, 2)), (64, 64, False, (1, 10)), (130, 65, False, (1, 64)),
+    (64 * 70, 70, True, (1, 3)), (200, 512, False, (1, 10)), (64 * 66, 512, True, (1, 7)),
+    (64 * 130 - 3, 64, True, (1, 4)), (100, 513, False, (1, 10)),
+])
+def test_topk_scores_of_one_upper_half(S_q, nKB, causal, keep):
+    """Scores that agree in the upper 32 bits of their doubles (they differ by
+    2^-27 of themselves and less), some of them equal, one sign or both, and
+    with infinities among them: the boundary lies between neighbours."""
+    rng = np.random.default_rng(nKB)
+    S_k, D = nKB * 64, 64
+    q = torch.zeros((1, 2, S_q, D), dtype=torch.bfloat16)
+    k = torch.zeros((1, 2, S_k, D), dtype=torch.bfloat16)
+    q[..., 0], q[..., 1] = 1.0, 2.0 ** -20
+    k[:, 0, :, 0] = 1.0
+    sign = np.repeat(rng.choice([-1.0, 1.0], nKB), 64)
+    k[:, 1, :, 0] = torch.from_numpy(sign).to(torch.bfloat16)
+    k[..., 1] = torch.from_numpy(np.repeat(rng.integers(0, 100, nKB) / 128.0, 64)).to(torch.bfloat16)
+    s = steel()
+    for inf in (False, True):
+        if inf and nKB > 2:
+            k[:, :, 64:128, 0] = float("inf")
+        got = s.topk_block_mask(q.cuda(), k.cuda(), *keep, causal=causal).cpu().numpy()
+        with np.errstate(invalid="ignore"):
+            want = oracle.topk_meanpool_mask(q, k, *keep, causal)
+        assert np.array_equal(got, want), f"inf={inf}: {int((got != want).sum())} mask bytes differ"
