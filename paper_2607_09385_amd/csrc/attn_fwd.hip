@@ -604,7 +604,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
   if (p.pack > 1) {
     AttnArgs ap = a;
     ap.order = w.order_p;
-    ap.n_items = a.coord ? nullptr : w.n_items + kPackItems;  // 0 when k_bucket handed them to the single-head list
+    ap.n_items = a.coord ? nullptr : w.n_items + kPackItems;  // 0 when they go with the single heads
     ap.units = p.B * (p.Hq / p.pack);
     hipError_t e = hipSuccess;
     if (D == 128 && p.pack == 4 && (size_t)p.S_q * D * 4 < (1ull << 31) && (PREC != kBf16 || p.NP > kFewPacks))

@@ -513,36 +513,44 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
 }
 
 // Combines the segments of split lists: with M = max m_s over the segments and
-// w_s = 2^(m_s - M), O = sum w_s O_s / sum w_s l_s.  One thread per row and 4
-// columns, the loads of 8 segments in flight; the parts are read once (2 MB
-// for 128 rows of 32 segments: latency, ~4 us).
+// w_s = 2^(m_s - M), O = sum w_s O_s / sum w_s l_s.  One wave per row: lane s
+// holds segment s's m, l and weight (at most 64 segments), then every lane
+// adds its D/64 columns over the segments, 8 loads in flight.  Latency bound:
+// the parts of 128 rows are 2 MB.
 template <int D>
 __global__ __launch_bounds__(256) void k_attn_join(AttnArgs a) {
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long r = idx / (D / 4);
+  constexpr int V = D / 64;
+  typedef float vec __attribute__((ext_vector_type(V)));
+  const int lane = threadIdx.x & 63;
+  const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= a.part_rows) return;
-  const int c = (int)(idx - r * (D / 4)) * 4;
   const float* ml = a.part + (size_t)a.ns * a.part_rows * D;
-  float M = -FLT_MAX;
-  for (int s = 0; s < a.ns; ++s) M = fmaxf(M, ml[2 * ((size_t)s * a.part_rows + r)]);
-  float ls = 0.f;
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  const size_t at = 2 * ((size_t)min(lane, a.ns - 1) * a.part_rows + r);
+  const float m = ml[at];
+  float M = m;
+  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+  const float w = lane < a.ns ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+  float ls = w * ml[at + 1];
+  for (int off = 32; off > 0; off >>= 1) ls += __shfl_xor(ls, off);
+  const float* src = a.part + (size_t)r * D + V * lane;
+  const size_t step = (size_t)a.part_rows * D;
+  float v[V] = {};
 #pragma unroll 8
   for (int s = 0; s < a.ns; ++s) {
-    const size_t row = (size_t)s * a.part_rows + r;
-    const float w = __builtin_amdgcn_exp2f(ml[2 * row] - M);
-    ls += w * ml[2 * row + 1];
-    v += w * *(const f32x4*)(a.part + row * D + c);
+    const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s));
+    const vec o = *(const vec*)(src + s * step);
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] += ws * o[e];
   }
   const float inv = ls > 0.f ? 1.f / ls : 0.f;
   const size_t row = (size_t)a.row0 + r;
-  if (a.lse != nullptr && c == 0)
+  if (a.lse != nullptr && lane == 0)
     a.lse[row] = ls > 0.f ? (M + log2f(ls)) * 0.69314718055994531f : -INFINITY;
-  if (a.out_bf16)
-    *(bf16x4*)((__bf16*)a.out + row * D + c) =
-        bf16x4{(__bf16)(v[0] * inv), (__bf16)(v[1] * inv), (__bf16)(v[2] * inv), (__bf16)(v[3] * inv)};
-  else
-    *(f32x4*)(a.out + row * D + c) = v * inv;
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    if (a.out_bf16) ((__bf16*)a.out)[row * D + V * lane + e] = (__bf16)(v[e] * inv);
+    else a.out[row * D + V * lane + e] = v[e] * inv;
+  }
 }
 
 template <int D, int PACK, int ST, int WPE>
@@ -568,7 +576,7 @@ hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, 
 }
 
 hipError_t launch_attention_join(const AttnArgs& a, int D, hipStream_t s) {
-  const dim3 grid((unsigned)((a.part_rows * (D / 4) + 255) / 256));
+  const dim3 grid((unsigned)((a.part_rows + 3) / 4));
   if (D == 64) hipLaunchKernelGGL(k_attn_join<64>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(k_attn_join<128>, grid, dim3(256), 0, s, a);
   return hipGetLastError();

@@ -203,7 +203,7 @@ __host__ __device__ inline int bucket_start(int heads, int rg, int mb) {
 hipError_t launch_attn_index(const Problem& p, const uint8_t* mask, const IndexBuffers& w,
                              hipStream_t stream);
 
-// Enqueue the build of the public index (row_ptr, col, order_s).
+// Enqueue the build of the public index (row_ptr, col, order).
 hipError_t launch_block_index(const Problem& p, const uint8_t* mask, const PublicIndex& w,
                               hipStream_t stream);
 
