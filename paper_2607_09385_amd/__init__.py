@@ -11,6 +11,7 @@ the library's HIP kernels.
 """
 from __future__ import annotations
 
+import contextlib
 import math
 from typing import Optional
 
@@ -23,22 +24,42 @@ STEEL_FP8 = 2
 STEEL_FP8_PV = 4
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+_stay = contextlib.nullcontext()
+
+
+def _on(device):
+    """The device made current for a call: nothing to do when it is already
+    (switching it and back takes longer than the rest of a small call)."""
+    torch = _torch()
+    if device.index is not None and device.index == torch.cuda.current_device():
+        return _stay
+    return torch.cuda.device(device)
 
 
 def _stream_handle(stream=None) -> int:
+    """Handle of the given stream, or of the current device's current one."""
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return int(stream.cuda_stream)
 
 
 def _check_bf16(name, t, ndim=4):
     torch = _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be on a GPU device (got {t.device})")
     if t.dtype != torch.bfloat16:
         raise ValueError(f"{name} must be bfloat16 (got {t.dtype})")
@@ -74,7 +95,7 @@ def attn_fwd(q, k, v, block_mask=None, *, scale: Optional[float] = None, causal:
         _check_bf16(name, t)
     B, Hq, S_q, D = q.shape
     Bk, Hkv, S_k, Dk = k.shape
-    if tuple(v.shape) != tuple(k.shape) or Bk != B or Dk != D:
+    if v.shape != k.shape or Bk != B or Dk != D:
         raise ValueError(f"shape mismatch: q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)}")
     if q.device != k.device or q.device != v.device:
         raise ValueError("q, k and v must be on the same device")
@@ -94,7 +115,7 @@ def attn_fwd(q, k, v, block_mask=None, *, scale: Optional[float] = None, causal:
         out = torch.empty((B, Hq, S_q, D), dtype=torch.float32, device=q.device)
     else:
         _check_out(out, (B, Hq, S_q, D), q.device)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _lib.load().steel_attn_fwd(
             q.data_ptr(), k.data_ptr(), v.data_ptr(), mask_ptr, out.data_ptr(),
             B, Hq, Hkv, S_q, S_k, D, blk, float(scale), 1 if causal else 0, _stream_handle(stream))
@@ -116,7 +137,7 @@ def attn_fwd_lse(q, k, v, block_mask=None, *, scale: Optional[float] = None, cau
         _check_bf16(name, t)
     B, Hq, S_q, D = q.shape
     Bk, Hkv, S_k, Dk = k.shape
-    if tuple(v.shape) != tuple(k.shape) or Bk != B or Dk != D:
+    if v.shape != k.shape or Bk != B or Dk != D:
         raise ValueError(f"shape mismatch: q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)}")
     if q.device != k.device or q.device != v.device:
         raise ValueError("q, k and v must be on the same device")
@@ -152,7 +173,7 @@ def attn_fwd_lse(q, k, v, block_mask=None, *, scale: Optional[float] = None, cau
     if lse.dtype != torch.float32 or tuple(lse.shape) != (B, Hq, S_q) or not lse.is_contiguous() \
             or lse.device != q.device:
         raise ValueError("lse must be a contiguous float32 tensor [B, Hq, S_q] on q's device")
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _lib.load().steel_attn_fwd_ex(
             q.data_ptr(), k.data_ptr(), v.data_ptr(), mask_ptr, out.data_ptr(), lse.data_ptr(),
             B, Hq, Hkv, S_q, S_k, D, blk, float(scale), 1 if causal else 0, int(causal_offset),
@@ -179,7 +200,7 @@ def attn_merge(o_parts, lse_parts, *, out=None, lse_out=None, stream=None):
         out = torch.empty(o_parts.shape[1:], dtype=torch.float32, device=o_parts.device)
     if lse_out is None:
         lse_out = torch.empty(lse_parts.shape[1:], dtype=torch.float32, device=o_parts.device)
-    with torch.cuda.device(o_parts.device):
+    with _on(o_parts.device):
         st = _lib.load().steel_attn_merge(o_parts.data_ptr(), lse_parts.data_ptr(), n, rows, D,
                                           out.data_ptr(), lse_out.data_ptr(), _stream_handle(stream))
     _lib.check(st)
@@ -197,7 +218,7 @@ def attn_fwd_window(q, k, v, window_blocks: int, sink_blocks: int = 0, *,
         _check_bf16(name, t)
     B, Hq, S_q, D = q.shape
     Bk, Hkv, S_k, Dk = k.shape
-    if tuple(v.shape) != tuple(k.shape) or Bk != B or Dk != D:
+    if v.shape != k.shape or Bk != B or Dk != D:
         raise ValueError(f"shape mismatch: q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)}")
     if q.device != k.device or q.device != v.device:
         raise ValueError("q, k and v must be on the same device")
@@ -207,7 +228,7 @@ def attn_fwd_window(q, k, v, window_blocks: int, sink_blocks: int = 0, *,
         out = torch.empty((B, Hq, S_q, D), dtype=torch.float32, device=q.device)
     else:
         _check_out(out, (B, Hq, S_q, D), q.device)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _lib.load().steel_attn_fwd_window(
             q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, Hq, Hkv, S_q, S_k, D, blk,
             float(scale), 1 if causal else 0, int(window_blocks), int(sink_blocks),
@@ -233,7 +254,7 @@ def topk_block_mask(q, k, keep_num: int = 1, keep_den: int = 10, *, causal: bool
         out = torch.empty((B, Hq, nQB, nKB), dtype=torch.uint8, device=q.device)
     elif out.dtype != torch.uint8 or tuple(out.shape) != (B, Hq, nQB, nKB) or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous uint8 tensor [{B}, {Hq}, {nQB}, {nKB}]")
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _lib.load().steel_topk_block_mask(
             q.data_ptr(), k.data_ptr(), B, Hq, Hkv, S_q, S_k, D, blk, 1 if causal else 0,
             int(keep_num), int(keep_den), out.data_ptr(), _stream_handle(stream))
@@ -258,7 +279,7 @@ def block_index(block_mask, B: int, Hq: int, S_q: int, S_k: int, *, causal: bool
     row_ptr = torch.empty(R + 1, dtype=torch.int32, device=device)
     col = torch.empty(max(R * nKB, 1), dtype=torch.int32, device=device)
     order = torch.empty(R, dtype=torch.int32, device=device)
-    with torch.cuda.device(device):
+    with _on(device):
         st = _lib.load().steel_block_index(
             None if block_mask is None else block_mask.data_ptr(), B, Hq, S_q, S_k, blk,
             1 if causal else 0, row_ptr.data_ptr(), col.data_ptr(), order.data_ptr(),
@@ -291,7 +312,7 @@ class Plan:
         self.shape = (B, Hq, Hkv, S_q, S_k)
         self.causal, self.blk, self.device = bool(causal), blk, device
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        with torch.cuda.device(device):
+        with _on(device):
             if window is not None:
                 if block_mask is not None:
                     raise ValueError("pass either block_mask or window, not both")
@@ -322,7 +343,7 @@ class Plan:
             out = torch.empty((B, Hq, S_q, D), dtype=torch.float32, device=q.device)
         else:
             _check_out(out, (B, Hq, S_q, D), q.device)
-        with torch.cuda.device(q.device):
+        with _on(q.device):
             st = _lib.load().steel_attn_run(
                 q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, Hq, Hkv, S_q, S_k,
                 D, self.blk, float(scale), 1 if self.causal else 0, self.workspace.data_ptr(),
