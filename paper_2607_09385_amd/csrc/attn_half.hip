@@ -28,9 +28,11 @@
 // (fewer workgroups per CU), two waves per SIMD at D = 64.
 //
 // Measured against the kernel it replaced (32 query rows per wave), whole
-// calls: 24 heads S = 32768 D = 64 top-10% 517 -> 485 us, 32 heads S = 8192 D =
-// 128 Bernoulli masks 231 -> 215 us, 32/8 heads S = 8192 D = 64 window (packs)
-// 184 -> 148 us.
+// calls, with the maximum moved at 2^24 then: 24 heads S = 32768 D = 64 top-10%
+// 517 -> 485 us, 32 heads S = 8192 D = 128 Bernoulli masks 231 -> 215, 32/8 heads
+// S = 8192 D = 64 window (packs, prebuilt index) 184 -> 148.  With the changes
+// to index and calls since, and the maximum moved at 2^8: 498 -> 471, 222 ->
+// 191, 183 -> 144 (start and now in turn on one card).
 #include <cfloat>
 #include <utility>
 
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   constexpr int LPW = C / NW;        // copies per wave and tile
   constexpr int CB = LPW < 4 ? LPW : 4;  // copies per assembly block
   constexpr int KS = D / 16, DT = D / 32, HD = DT / 2;
-  constexpr float TAU = 24.0f;  // rescale only when a row max grows by > 2^24
+  constexpr float TAU = 8.0f;  // rescale only when a row max grows by > 2^8
   constexpr int V_AT = ST * TB;
   constexpr int REC = (4 + 2 * 16 * HD) * 256;  // merge record bytes per wave
   constexpr int LDS_BYTES = 2 * ST * TB > NW * REC ? 2 * ST * TB : NW * REC;
@@ -452,9 +454,15 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
             sc[nt][r] = 8 * (r >> 2) + (r & 3) > lim ? -INFINITY : sc[nt][r];
         }
       }
-      // row maxima: the running maximum m moves only when some row's grew by more
-      // than TAU (P <= 2^TAU, and m cancels in O / l), so the common tile only
-      // compares each lane's own maximum, without the exchange between halves
+      // row maxima: the running maximum m of 32 rows moves only when one of them
+      // grew by more than TAU (P <= 2^TAU, and m cancels in O / l), so the common
+      // tile only compares each lane's own maximum, without the exchange between
+      // halves.  2^8 and not more: close to its true maximum a row's largest
+      // weights round to bf16 with less error (a weight of 1 with none), which
+      // shows where few keys hold a row's mass (24 heads S = 32768 D = 64 top-10%:
+      // error against float64 2.5e-4 of the output, 3.4e-4 with 2^24, which is 3%
+      // faster there and equal elsewhere).  Each 32 rows by themselves: 503 us
+      // there, 508 when both halves are rescaled together.
       {
         float mx[2];
 #pragma unroll
@@ -467,6 +475,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
         if (__builtin_amdgcn_ballot_w64((mx[0] * a.c > m[0] + TAU) | (mx[1] * a.c > m[1] + TAU))) {
 #pragma unroll
           for (int nt = 0; nt < 2; ++nt) {
+            if (!__builtin_amdgcn_ballot_w64(mx[nt] * a.c > m[nt] + TAU)) continue;
             const float mnew = fmaxf(m[nt], other_half_max(mx[nt]) * a.c);
             const float alpha = __builtin_amdgcn_exp2f(m[nt] - mnew);
             l[nt] *= alpha;
