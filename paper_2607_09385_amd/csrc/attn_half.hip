@@ -388,9 +388,14 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   wait_vm<0>();
   h_barrier();
 
-  constexpr int KA = 3;      // K fragments read ahead
-  constexpr int NQ = 2 * DT;               // V^T fragments
-  constexpr int VA = 3;     // and read ahead
+  // K and V^T fragments read ahead of their MFMA.  At D = 128, where O takes
+  // 128 registers, two leave the scheduler more room than three (32 heads S =
+  // 8192 Bernoulli masks 192 -> 188 us, 1000 queries against 12000 keys 228.5 ->
+  // 226.5); at D = 64 three are the better count (469 us against 471 on the 24
+  // heads' top-10%, four: 469).
+  constexpr int KA = D == 128 ? 2 : 3;
+  constexpr int NQ = 2 * DT;
+  constexpr int VA = KA;
   if (L > 0) {
 #pragma clang loop unroll(disable)
     for (int i = 0;; ++i) {
