@@ -63,7 +63,7 @@ def test_against_oracle(case):
 @pytest.mark.parametrize("D,Hq,Hkv", [(64, 2, 2), (128, 2, 2), (64, 8, 2), (128, 8, 2)])
 def test_growing_maxima(D, Hq, Hkv):
     """Scores that grow along the keys move every row's running maximum by far
-    more than the deferred rescale allows (2^24), several times per row."""
+    more than the deferred rescale allows (2^8), several times per row."""
     S = 512
     q, k, v = small_qkv(3, 1, Hq, Hkv, S, S, D)
     grow = (1.0 + 40.0 * torch.arange(S) / S)[None, None, :, None]
@@ -71,6 +71,20 @@ def test_growing_maxima(D, Hq, Hkv):
     out = steel().attn_fwd(q.cuda(), k.cuda(), v.cuda(), scale=D ** -0.5, causal=False)
     # scores up to ~150: their bf16-operand fp32 sums are exact to ~2e-5, the
     # weights to 2^-9 as everywhere
+    check(out, oracle.attention(q, k, v, None, D ** -0.5, False, 64), f"D={D}")
+
+
+@pytest.mark.parametrize("half", [0, 1])
+@pytest.mark.parametrize("D", [64, 128])
+def test_growing_maxima_of_one_half(D, half):
+    """Only 32 of a block's 64 rows have growing maxima; the others' stay."""
+    S = 512
+    q, k, v = small_qkv(4, 1, 1, 1, S, S, D)
+    grow = (1.0 + 40.0 * torch.arange(S) / S)[None, None, :, None]
+    still = (torch.arange(S) // 32 % 2 != half)[None, None, :, None]
+    q = torch.where(still, q.float() / 64, q.float()).to(torch.bfloat16)
+    k = (k.float() * grow).to(torch.bfloat16)
+    out = steel().attn_fwd(q.cuda(), k.cuda(), v.cuda(), scale=D ** -0.5, causal=False)
     check(out, oracle.attention(q, k, v, None, D ** -0.5, False, 64), f"D={D}")
 
 
