@@ -47,7 +47,8 @@ PEAK_TFLOPS = 256 * 2.4e9 * 4096 / 1e12     # 2516.6
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_traffic.json")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2607_09385_amd", "csrc", f)
-               for f in ("attn_common.h", "attn_fwd.hip", "attn_ws.hip", "block_index.hip")]
+               for f in ("attn_common.h", "attn_fwd.hip", "attn_half.hip", "attn_ws.hip",
+                         "block_index.hip")]
 
 
 def live_tile_counts(mask, B, Hq, S_q, S_k, causal, blk=64):
@@ -94,28 +95,30 @@ def traffic_for(workload):
 # dot2 for the row sum.  Cycles per 64-lane instruction measured by
 # `bench.py --mfma-peak` (steel_valu_rate, shader clock, from the first wave's
 # start to the last wave's end): a SIMD with eight resident waves sustains
-# v_exp_f32 every 5.26 cycles and v_fma_f32 every 1.98, while a single wave
-# issues them only every 12.0 and 8.5 cycles (the other three instructions are
-# taken at the fma's rate).
+# v_exp_f32 every 5.26 cycles and v_fma_f32 every 1.98.  A single wave issues
+# them every 8 and 4 cycles in long unrolled runs (steel_valu_rate reads 12.0
+# and 8.5 there: its short loop's own instructions count), and an MFMA holds
+# the wave's issue for 8 (the other three instructions are taken at the fma's
+# rate).
 VALU_CYCLES_SIMD = 5.26 + 1.98 + 1.5 * 1.98       # per 64 elements, SIMD throughput
-VALU_CYCLES_ONE_WAVE = 12.0 + 8.5 + 1.5 * 8.5     # per 64 elements, issued by one wave
+VALU_CYCLES_ONE_WAVE = 8.0 + 4.0 + 1.5 * 4.0     # per 64 elements, issued by one wave
 
 
 def valu_bound(n_live, D):
     """The softmax alone on all 1,024 SIMDs at 2.4 GHz: at the SIMD's VALU
     throughput (the plain-ALU bound beside the MFMA one), and issued by one
     wave per SIMD at the single-wave rate together with that wave's own score
-    MFMAs, which hold its issue (the structure of the wave-specialised kernel,
+    MFMAs (the structure of the wave-specialised kernel,
     whose one S-wave per head computes the scores and the softmax of 64 rows)."""
     elems = n_live * 64 * 64
     us = elems * VALU_CYCLES_SIMD / 64 / (256 * 4 * 2.4e9) * 1e6
-    one = (elems * VALU_CYCLES_ONE_WAVE / 64 + n_live * (D // 4) * 32) / (256 * 4 * 2.4e9) * 1e6
+    one = (elems * VALU_CYCLES_ONE_WAVE / 64 + n_live * (D // 4) * 8) / (256 * 4 * 2.4e9) * 1e6
     return {"bound": "alu", "us": round(us, 1),
             "model": "per live element: exp2 + fma + half max3 + half cvt_pk_bf16 + half dot2 at the measured "
                      "SIMD rates (v_exp_f32 5.26, v_fma_f32 1.98 cycles per 64 lanes)",
             "one_wave_softmax_us": round(one, 1),
-            "one_wave_model": "same instructions issued by one wave per SIMD (v_exp_f32 every 12.0, others every "
-                              "8.5 cycles) plus that wave's D/4 score MFMAs per tile (32 cycles each)",
+            "one_wave_model": "same instructions issued by one wave per SIMD (v_exp_f32 every 8, others every "
+                              "4 cycles) plus that wave's D/4 score MFMAs per tile (8 issue cycles each)",
             "mfma_us_at_peak": round(4.0 * 64 * 64 * D * n_live / PEAK_TFLOPS / 1e6, 1)}
 
 
@@ -599,7 +602,7 @@ def bench_workload(name, steps, warmup, cpu_seconds, want_cpu, clock_warmup=0.5)
             "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_TFLOPS, 4),
             "traffic": traffic,
-            "kernel": "attention run (k_attn_ws for uniform head packs of 4 at D=128, k_attn for the other items), index prebuilt",
+            "kernel": "attention run (k_attn_ws for uniform head packs of 4 at D=128, k_attn_h for the other items), index prebuilt",
             "run_us": round(run_s * 1e6, 2),
             "algorithmic_flops_per_run": f_live,
         },

@@ -3,11 +3,12 @@
 // softmax, a second wave on the same SIMD accumulates O += V P and writes the
 // output.
 //
-// Same mathematics as k_attn (the online-softmax recurrence of Algorithm 1
-// over the live tiles of a query block, Section IV-A masking, Section IV-C
-// work order).  The schedule is built around how a CDNA4 SIMD issues: a
-// wave issues in order, one VALU instruction every 8-16 cycles on its own,
-// and an MFMA waits for the SIMD's matrix core, so a wave that mixes score
+// The online-softmax recurrence of Algorithm 1 over the live tiles of a query
+// block (Section IV-A masking, Section IV-C work order).  The schedule is
+// built around how a CDNA4 SIMD issues: a wave issues in order, one VALU
+// instruction every 4 cycles on its own (an exponential every 8, and half that
+// rate beside another wave's MFMA stream), and an MFMA waits for the SIMD's
+// matrix core, so a wave that mixes score
 // MFMAs into its softmax stalls whenever another wave's MFMAs hold the
 // matrix core.  Kept apart, one wave's softmax runs while the matrix core
 // serves the other wave's MFMAs.  Algorithm 1 has three stages
@@ -27,10 +28,10 @@
 //   a SIMD share the matrix core and each fills the other's VALU cycles.
 //
 // The stream is the concatenation of the workgroup's items (a query block of
-// a pack of 4 heads sharing one live list), taken in the same XCD-aware,
-// heaviest-first, serpentine order as the other kernels; item boundaries need
-// no pipeline drain: the O-waves write an item's output while the S-waves
-// already compute the next item's first tile.
+// a pack of 4 heads sharing one live list), taken heaviest first, in
+// XCD-aware groups and serpentine rounds; item boundaries need no pipeline
+// drain: the O-waves write an item's output while the S-waves already compute
+// the next item's first tile.
 //
 // LDS (152 KiB): a 3-stage K ring and a 2-stage V ring (16 KiB tiles, the
 // swizzled layout of attn_common.h), P double-buffered per head (8 KiB), and

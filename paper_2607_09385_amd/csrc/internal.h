@@ -168,7 +168,11 @@ struct SplitPlan {
 SplitPlan plan_split(const Problem& p);
 
 // Up to this many head packs of 4 at D = 128 (bf16) are run two heads to a
-// workgroup instead of four: a persistent workgroup per CU leaves CUs idle.
+// workgroup (k_attn_h) instead of four (k_attn_ws): with one persistent
+// workgroup per CU and no more packs than CUs, CUs stand idle or wait for the
+// longest pack.  1000 queries against 11000 keys with 32/8 heads (128 packs):
+// 328 us by fours, 227 by twos; S = 4096 causal (512 packs) 126 by fours, 144
+// by twos.
 constexpr int kFewPacks = 256;
 
 __host__ __device__ inline int nchunks(int n) { return (n + kChunk - 1) / kChunk; }
