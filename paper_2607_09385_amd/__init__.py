@@ -39,10 +39,12 @@ _stay = contextlib.nullcontext()
 
 
 def _on(device):
-    """The device made current for a call: nothing to do when it is already
-    (switching it and back takes longer than the rest of a small call)."""
+    """The device (a torch.device, an index or a name) made current for a call:
+    nothing to do when it is already (switching it and back takes longer than
+    the rest of a small call).  Anything but a GPU is refused."""
     torch = _torch()
-    if device.index is not None and device.index == torch.cuda.current_device():
+    if isinstance(device, torch.device) and device.type == "cuda" \
+            and device.index == torch.cuda.current_device():
         return _stay
     return torch.cuda.device(device)
 
