@@ -36,8 +36,9 @@ struct AttnArgs {
   const float* f8_scale;    //   and the per-(b, g) inverse scales {1/s_k, 1/s_v}
   // Block mask from coordinates (every block, or with win_blocks > 0 the window
   // and sink blocks of Problem): nothing was indexed, rows and their live lists
-  // are computed in the kernel; units: head packs (or heads) per query block
-  int coord, win_blocks, sink_blocks, units;
+  // are computed in the kernel; units: head packs (or heads) per query block,
+  // range: their order (coord_range)
+  int coord, win_blocks, sink_blocks, units, range;
   // SplitPlan: segments per list, heads per tile, the batch's first unit, its
   // rows, and its partial results: O [ns][rows][D], then {m, l} [ns][rows]
   int ns, hp, unit0;
@@ -101,24 +102,11 @@ __device__ __forceinline__ uint32_t live_entry(const AttnArgs& a, const LiveRow&
   return (uint32_t)kb | (part ? 0x80000000u : 0u);
 }
 
-// Items of a list without an index.  Heaviest query blocks first (the live
-// count grows with the query block but for a window's first blocks), the
-// units of one query block next to each other.  The workgroups of XCD x take
-// positions 0, 1, ... of its share: with the units a multiple of 8, units x,
-// x + 8, ... (its L2 then holds the keys and values of few heads), else
-// every eighth item.  Item: unit * nQB + query block; -1 past the end.
-__device__ __forceinline__ int coord_items(const AttnArgs& a, int x) {  // of XCD x
-  const int n = a.units * a.nQB;
-  return a.units % 8 == 0 ? n / 8 : (n - x + 7) / 8;
+__device__ __forceinline__ int coord_items(const AttnArgs& a, int x) {
+  return coord_items(a.units, a.nQB, a.range, x);
 }
 __device__ __forceinline__ int coord_item(const AttnArgs& a, int x, int pos) {
-  if (pos >= coord_items(a, x)) return -1;
-  if (a.units % 8 == 0) {
-    const int per = a.units / 8, k = pos / per;
-    return (x + 8 * (pos - k * per)) * a.nQB + (a.nQB - 1 - k);
-  }
-  const int idx = 8 * pos + x, k = idx / a.units;
-  return (idx - k * a.units) * a.nQB + (a.nQB - 1 - k);
+  return coord_item(a.units, a.nQB, a.range, x, pos);
 }
 
 __device__ __forceinline__ float other_half_max(float x) {

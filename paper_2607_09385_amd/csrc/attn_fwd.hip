@@ -584,6 +584,7 @@ static hipError_t launch_split(const Problem& p, AttnArgs a, const SplitPlan& sp
   for (int u = 0; u < sp.units; u += batch) {
     a.unit0 = u;
     a.units = sp.units - u < batch ? sp.units - u : batch;
+    a.range = (a.units + 7) / 8 * 8;
     a.part_rows = (long long)a.units * heads * p.S_q;
     a.row0 = (long long)u * heads * p.S_q;
     const int items = a.units * p.nQB;
@@ -606,6 +607,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
     ap.order = w.order_p;
     ap.n_items = a.coord ? nullptr : w.n_items + kPackItems;  // 0 when they go with the single heads
     ap.units = p.B * (p.Hq / p.pack);
+    ap.range = coord_range(ap.units, p.nQB, p.causal, p.win_blocks > 0, false);
     hipError_t e = hipSuccess;
     if (D == 128 && p.pack == 4 && (size_t)p.S_q * D * 4 < (1ull << 31) && (PREC != kBf16 || p.NP > kFewPacks))
       e = launch_attention_ws(ap, PREC, s);
@@ -618,6 +620,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
   a.n_items = w.n_items;
   a.bucket = w.bucket;
   a.units = p.B * p.Hq;
+  a.range = coord_range(a.units, p.nQB, p.causal, p.win_blocks > 0, true);
   int grid = p.R;
   if (a.coord) {
     grid = (p.R + 7) / 8 * 8;

@@ -175,6 +175,53 @@ SplitPlan plan_split(const Problem& p);
 // by twos.
 constexpr int kFewPacks = 256;
 
+// Order of the items of a call without an index (unit * nQB + query block; a
+// unit is a head, or the heads of a pack or of a tile).  XCD x takes positions
+// 0, 1, ... of its share, coord_items of them; coord_item is -1 past the end.
+// range > 0: the units are taken in ranges of that many (a multiple of 8);
+//   within a range heaviest query blocks first (the live count grows with the
+//   query block but for a window's first blocks), the units of one query block
+//   next to each other.  XCD x takes every eighth item, which are those of the
+//   units x, x + 8, ... of a range of whole eights.
+// range == 0: unit by unit, XCD x takes the x-th eighth.
+__host__ __device__ inline int coord_items(int units, int nQB, int range, int x) {
+  const int n = units * nQB, per = (n + 7) / 8;
+  if (range > 0) return (n - x + 7) / 8;
+  const int left = n - x * per;
+  return left < 0 ? 0 : left < per ? left : per;
+}
+__host__ __device__ inline int coord_item(int units, int nQB, int range, int x, int pos) {
+  if (pos >= coord_items(units, nQB, range, x)) return -1;
+  if (range == 0) {
+    const int idx = x * ((units * nQB + 7) / 8) + pos, u = idx / nQB;
+    return u * nQB + (nQB - 1 - (idx - u * nQB));
+  }
+  const int idx = 8 * pos + x, u0 = idx / (range * nQB) * range;
+  const int in = idx - u0 * nQB, n = units - u0 < range ? units - u0 : range, k = in / n;
+  return (u0 + in - k * n) * nQB + (nQB - 1 - k);
+}
+
+// The range, for an L2 of 4 MiB per XCD: the workgroups an XCD runs at one time
+// (32 to 192) should read the keys and values of few units.  Lists of equal
+// length (no causal limit) lose nothing by short ranges: 128 items per XCD.
+// Causal ones restart with the heaviest query blocks in each range, so ranges
+// are longer: 512 items.  32 heads D = 128, batch of 16, S = 2048, no causal
+// limit: 2,315 us as one range, 1,206 with 128 items, 1,888 with 512 (an index
+// per call, head by head: 1,461); causal 1,155, 730 and 731 (956); batch of 8,
+// S = 4096, window of 16 blocks: 1,060, 674 and 742 (874).
+// Windows over single heads, not a multiple of 8: eight contiguous shares,
+// since every eighth item would have each XCD read every head (6 heads S =
+// 32768 D = 128, 16 blocks: 244 -> 129 us; 20 heads batch of 3 S = 4096: 255 ->
+// 155).  From 1,024 items on: below, a share without a unit's light first
+// blocks takes a round longer (282 items 18.8 -> 22.4 us).  Packs stay in ranges
+// (12/3 heads batch of 3 S = 4096: 83 us against 101).
+inline int coord_range(int units, int nQB, bool causal, bool window, bool single) {
+  if (window && single && units % 8 != 0 && units * nQB >= 1024) return 0;
+  const int items = causal || window ? 512 : 128;
+  const int per = (items + nQB - 1) / nQB, all = (units + 7) / 8;
+  return 8 * (per < all ? per : all);
+}
+
 __host__ __device__ inline int nchunks(int n) { return (n + kChunk - 1) / kChunk; }
 
 // Set in cnt[r] of the first row of a head pack whose rows all have the same

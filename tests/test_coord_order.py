@@ -1,0 +1,73 @@
+"""The order in which calls without an index deal their items to the XCDs, on
+the CPU: the functions of csrc/internal.h compiled for the host."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2607_09385_amd import build
+
+SOURCE = """
+#include "internal.h"
+extern "C" {
+int items(int units, int nQB, int range, int x) { return steel::coord_items(units, nQB, range, x); }
+void order(int units, int nQB, int range, int x, int n, int* out) {
+  for (int i = 0; i < n; ++i) out[i] = steel::coord_item(units, nQB, range, x, i);
+}
+int range(int units, int nQB, int causal, int window, int single) {
+  return steel::coord_range(units, nQB, causal, window, single);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("order")
+    src, so = os.path.join(d, "order.hip"), os.path.join(d, "order.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.run([build.hipcc(), "--offload-host-only", "-x", "hip", "-O1", "-std=c++17", "-fPIC", "-shared",
+                    "-I", build.CSRC, src, "-o", so], check=True, capture_output=True)
+    return ctypes.CDLL(so)
+
+
+def share(lib, units, nQB, rng, x):
+    n = lib.items(units, nQB, rng, x)
+    out = (ctypes.c_int * (n + 1))()
+    lib.order(units, nQB, rng, x, n + 1, out)
+    assert out[n] == -1  # past the end
+    return list(out[:n])
+
+
+@pytest.mark.parametrize("nQB", [1, 2, 7, 8, 33, 130])
+def test_every_item_once(lib, nQB):
+    for units in list(range(1, 26)) + [36, 64, 100]:
+        per = (units * nQB + 7) // 8  # positions the grids hold for an XCD
+        for rng in [0] + [8 * r for r in range(1, (units + 7) // 8 + 1)]:
+            shares = [share(lib, units, nQB, rng, x) for x in range(8)]
+            assert all(len(s) <= per for s in shares)
+            assert sorted(i for s in shares for i in s) == list(range(units * nQB)), (units, rng)
+
+
+@pytest.mark.parametrize("units,nQB,causal,window,single", [
+    (256, 32, False, False, True), (512, 32, True, False, True), (256, 64, True, True, True),
+    (64, 32, False, False, False), (250, 32, False, False, True), (6, 512, True, True, True)])
+def test_few_units_at_a_time(lib, units, nQB, causal, window, single):
+    """What an XCD runs at one time (128 items) reads the keys and values of
+    few units, where one range over all of them mixes up to units / 8 or more."""
+    rng = lib.range(units, nQB, causal, window, single)
+    most = 1 if rng == 0 else rng // 8
+    assert most <= 16
+    for x in range(8):
+        s = [i // nQB for i in share(lib, units, nQB, rng, x)]
+        # 128 items may straddle two ranges, and a last range that is no whole
+        # eights is shared by all XCDs
+        seen = max(len(set(s[i:i + 128])) for i in range(0, len(s), 64))
+        assert seen <= (2 * most if rng == 0 or units % 8 == 0 else most + rng), (x, seen)
+
+
+def test_small_calls_keep_one_range(lib):
+    for units, nQB in ((1, 8), (96, 8), (8, 64), (16, 47), (24, 64)):
+        assert lib.range(units, nQB, True, False, True) == (units + 7) // 8 * 8

@@ -97,6 +97,11 @@ def test_growing_maxima_of_one_half(D, half):
     (1, 4, 2, 320, 900, 128, True, 1000, 0),
     (9, 16, 4, 640, 640, 128, True, 2, 1),
     (1, 2, 2, 900, 100, 128, True, 2, 1),
+    # many heads: several ranges of them, the last a smaller one; contiguous
+    # shares of a window over heads that are no multiple of 8
+    (9, 17, 17, 960, 960, 64, False, 3, 1),
+    (3, 50, 50, 900, 960, 128, True, 2, 1),
+    (20, 32, 8, 900, 960, 64, False, 3, 1),
 ], ids=lambda c: "x".join(str(int(v)) for v in c))
 def test_coordinates_equal_mask_tensor(shape):
     """Bit for bit where the lists are not split (fewer than 16 key blocks)."""
