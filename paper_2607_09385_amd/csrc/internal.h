@@ -209,6 +209,9 @@ __host__ __device__ inline int coord_item(int units, int nQB, int range, int x, 
 // limit: 2,315 us as one range, 1,206 with 128 items, 1,888 with 512 (an index
 // per call, head by head: 1,461); causal 1,155, 730 and 731 (956); batch of 8,
 // S = 4096, window of 16 blocks: 1,060, 674 and 742 (874).
+// The ranges are of about one size: a last one of few heads would begin the
+// heaviest lists when the others end (24 heads batch of 3 S = 4096 causal, 8 + 1
+// heads per XCD: 225 us at D = 64, 192 as one range of 9).
 // Windows over single heads, not a multiple of 8: eight contiguous shares,
 // since every eighth item would have each XCD read every head (6 heads S =
 // 32768 D = 128, 16 blocks: 244 -> 129 us; 20 heads batch of 3 S = 4096: 255 ->
@@ -219,7 +222,8 @@ inline int coord_range(int units, int nQB, bool causal, bool window, bool single
   if (window && single && units % 8 != 0 && units * nQB >= 1024) return 0;
   const int items = causal || window ? 512 : 128;
   const int per = (items + nQB - 1) / nQB, all = (units + 7) / 8;
-  return 8 * (per < all ? per : all);
+  const int n = (2 * all + per) / (2 * per);  // all / per, rounded to nearest
+  return 8 * (n > 1 ? (all + n - 1) / n : all);
 }
 
 __host__ __device__ inline int nchunks(int n) { return (n + kChunk - 1) / kChunk; }

@@ -71,3 +71,14 @@ def test_few_units_at_a_time(lib, units, nQB, causal, window, single):
 def test_small_calls_keep_one_range(lib):
     for units, nQB in ((1, 8), (96, 8), (8, 64), (16, 47), (24, 64)):
         assert lib.range(units, nQB, True, False, True) == (units + 7) // 8 * 8
+
+
+@pytest.mark.parametrize("nQB", [8, 32, 47, 64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_ranges_are_of_about_one_size(lib, nQB, causal):
+    """The last range, which begins with its heaviest lists when the others
+    end, is no remainder of a unit or two per XCD."""
+    for units in range(8, 600, 8):
+        r = lib.range(units, nQB, causal, False, True) // 8
+        last = units // 8 % r or r
+        assert 2 * last >= r or r - last <= units // 8 // r, (units, r, last)
