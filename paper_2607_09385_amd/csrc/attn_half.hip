@@ -1,6 +1,6 @@
 // Fused sparse attention forward in bf16 on gfx950: two waves per query head,
 // each holding all 64 query rows of the block and taking half the keys of
-// every 64-key tile.
+// every 64-key tile; or, where workgroups are few, four, each with 32 rows.
 //
 // The online softmax of Algorithm 1 over the live tiles of a query block
 // (Section IV-A masking, Section IV-C work order), split over keys: wave kh of
@@ -123,12 +123,13 @@ __device__ __forceinline__ int opaque_lane() {
 
 // The row sums add the bf16-rounded P that the MFMAs consume (v_dot2 against
 // (1, 1)), so O / l weights the value rows exactly as used.
-__device__ __forceinline__ void add_rows(const bf16x8 (&pa)[2][2], float (&l)[2]) {
+template <int NT>
+__device__ __forceinline__ void add_rows(const bf16x8 (&pa)[2][NT], float (&l)[NT]) {
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       u32x4 w = __builtin_bit_cast(u32x4, pa[t][nt]);
       asm("" : "+v"(w));  // the packed words: the compiler would convert the weights again
 #pragma unroll
@@ -145,20 +146,27 @@ __device__ __forceinline__ void add_rows(const bf16x8 (&pa)[2][2], float (&l)[2]
 // l_1, O = w_0 O_0 + w_1 O_1.  Each wave finishes half of the d tiles: it
 // leaves the other half of its O, its m and its row sums in its LDS record
 // (record wave ^ 1 is its partner's) and reads its partner's.
-template <int D>
-__device__ __forceinline__ void merge_rows(const AttnArgs& a, f32x16 (&o)[2][D / 32], const float (&m)[2],
-                                           const float (&l)[2], char* smem, int wave, int kh, int lane,
+template <int D, int NT>
+__device__ __forceinline__ void merge_rows(const AttnArgs& a, f32x16 (&o)[NT][D / 32], const float (&m)[NT],
+                                           const float (&l)[NT], char* smem, int wave, int kh, int lane,
                                            size_t bh, int row0, int nrows, int seg) {
   constexpr int DT = D / 32, HD = DT / 2;
-  constexpr int REC = (4 + 2 * 16 * HD) * 256;
+  constexpr int REC = (4 + NT * 16 * HD) * 256;
   const int n = lane & 31, hf = lane >> 5;
   h_barrier();  // the ring is free
   float* mine = (float*)(smem + wave * REC) + lane * 4;
   const float* part = (const float*)(smem + (wave ^ 1) * REC) + lane * 4;
-  const float lt[2] = {half_pair_sum(l[0]), half_pair_sum(l[1])};
-  *(f32x4*)mine = f32x4{m[0], m[1], lt[0], lt[1]};
+  float lt[NT];
+  f32x4 ml_mine = {};
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+  for (int nt = 0; nt < NT; ++nt) {
+    lt[nt] = half_pair_sum(l[nt]);
+    ml_mine[nt] = m[nt];
+    ml_mine[2 + nt] = lt[nt];
+  }
+  *(f32x4*)mine = ml_mine;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int j = 0; j < HD; ++j) {
       const f32x16 lo = o[nt][j], hi = o[nt][HD + j];
@@ -173,7 +181,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, f32x16 (&o)[2][D /
   h_barrier();
   const f32x4 pm = *(const f32x4*)part;
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     const float mp = pm[nt], ltp = pm[2 + nt];
     const float M = fmaxf(m[nt], mp);
     const float w = __builtin_amdgcn_exp2f(m[nt] - M);
@@ -229,17 +237,20 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, f32x16 (&o)[2][D /
   }
 }
 
-// D: head dimension; PACK: heads per workgroup (2 PACK waves); ST: stages of
-// the K and of the V ring (1: K and V tiles refilled in turn behind two
+// D: head dimension; PACK: heads per workgroup; RH: row halves of a block with a
+// wave pair of their own (1: waves of 64 rows, 2: of 32; the same arithmetic,
+// bit for bit, since each 32 rows move their maximum by themselves); 2 RH PACK
+// waves; ST: stages of the K and of the V ring (1: K and V tiles refilled in turn behind two
 // barriers per tile; 2: both one tile ahead, one barrier); RAGGED: S_k is not
 // a multiple of the block; WPE: waves per SIMD the registers must allow.
-// Single heads take ST = 1: more workgroups per CU hide more than a second
-// stage does (S = 32768 top-10%: 501 us against 560, S = 8192 Bernoulli 219
-// against 248).  Packs take ST = 2: their workgroups share each tile between
+// Single heads with 64-row waves take ST = 1: more workgroups per CU hide more
+// than a second stage does (S = 32768 top-10%: 501 us against 560, S = 8192
+// Bernoulli 219 against 248).  Packs take ST = 2: their workgroups share each tile between
 // two heads, and two (D = 128) or three (D = 64) of them fit a CU either way.
-template <int D, int PACK, int ST, bool RAGGED, int WPE>
-__global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void k_attn_h(AttnArgs a) {
-  constexpr int NW = 2 * PACK;       // waves
+template <int D, int PACK, int RH, int ST, bool RAGGED, int WPE>
+__global__ __launch_bounds__(128 * RH * PACK) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void k_attn_h(AttnArgs a) {
+  constexpr int NW = 2 * RH * PACK;  // waves
+  constexpr int NT = 2 / RH;         // 32-row N-tiles of a wave
   constexpr int C = D / 8;           // 16-byte chunks per row = 1 KiB copies per tile
   constexpr int RB = D * 2;          // row bytes
   constexpr int TB = kBlk * RB;      // tile bytes
@@ -248,7 +259,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   constexpr int KS = D / 16, DT = D / 32, HD = DT / 2;
   constexpr float TAU = 8.0f;  // rescale only when a row max grows by > 2^8
   constexpr int V_AT = ST * TB;
-  constexpr int REC = (4 + 2 * 16 * HD) * 256;  // merge record bytes per wave
+  constexpr int REC = (4 + NT * 16 * HD) * 256;  // merge record bytes per wave
   constexpr int LDS_BYTES = 2 * ST * TB > NW * REC ? 2 * ST * TB : NW * REC;
   static_assert(LPW >= 1 && C % NW == 0, "tile copy split");
   __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
@@ -296,7 +307,8 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kh = wave & 1;
-  const int head = h0 + sub * PACK + (wave >> 1);
+  const int r0 = RH == 1 ? 0 : 32 * ((wave >> 1) & 1);  // the wave's first row of the block
+  const int head = h0 + sub * PACK + wave / (2 * RH);
   const int n = lane & 31, hf = lane >> 5;
   const size_t kvoff = ((size_t)b * a.Hkv + g) * a.S_k * D;
   const __bf16* kg = a.k + kvoff;
@@ -347,18 +359,19 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
     issue_copy(vg, V_AT, (int)(cw & 0x7fffffffu));
   }
   // Q rows as the B operand (lane: row 32*nt + n, d = 16*ks + 8*hf + 0..7)
-  bf16x8 qf[2][KS];
+  bf16x8 qf[NT][KS];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     // with hp heads in a tile its rows are consecutive rows of q; rows past the
     // end read the last one
-    const size_t row = hp > 1 ? (size_t)min(32 * nt + n, hp * a.S_q - 1) : (size_t)min(qb * kBlk + 32 * nt + n, a.S_q - 1);
+    const int br = r0 + 32 * nt + n;
+    const size_t row = hp > 1 ? (size_t)min(br, hp * a.S_q - 1) : (size_t)min(qb * kBlk + br, a.S_q - 1);
     const __bf16* qr = a.q + (((size_t)b * a.Hq + head) * a.S_q + row) * D + 8 * hf;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[nt][ks] = *(const bf16x8*)(qr + 16 * ks);
   }
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(qf[nt][ks]));
 
@@ -379,12 +392,15 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  f32x16 o[2][DT];
-  float m[2] = {-FLT_MAX, -FLT_MAX}, l[2] = {0.f, 0.f};
+  f32x16 o[NT][DT];
+  float m[NT], l[NT];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+  for (int nt = 0; nt < NT; ++nt) {
+    m[nt] = -FLT_MAX;
+    l[nt] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[nt][dt] = f32x16{};
+  }
   wait_vm<0>();
   h_barrier();
 
@@ -417,7 +433,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
         }
       }
       // S^T = K Q^T over this wave's 32 keys
-      f32x16 sc[2];
+      f32x16 sc[NT];
       asm volatile("" : "+v"(kbase), "+v"(vbase));
       {
         bf16x8 kf[KA];
@@ -427,7 +443,7 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
         h_static_for<KS>([&](auto kc) __attribute__((always_inline)) {
           constexpr int ks = decltype(kc)::value;
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt)
+          for (int nt = 0; nt < NT; ++nt)
             sc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks % KA], qf[nt][ks],
                                                              ks == 0 ? f32x16{} : sc[nt], 0, 0, 0);
           if constexpr (ks + KA < KS) {
@@ -448,8 +464,8 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
       if (cw >> 31) {  // element mask of a partial tile (Section IV-A case iii)
         const int kb = (int)(cw & 0x7fffffffu), ln = opaque_lane();
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-          int row = 32 * nt + (ln & 31);
+        for (int nt = 0; nt < NT; ++nt) {
+          int row = r0 + 32 * nt + (ln & 31);
           row = hp > 1 ? row % a.S_q : qb * kBlk + row;
           const int lim_abs = min(a.causal ? row + a.delta : INT_MAX - kBlk, a.S_k - 1);
           int lim = lim_abs - (kb * kBlk + 32 * kh + 4 * (ln >> 5));
@@ -469,18 +485,20 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
       // faster there and equal elsewhere).  Each 32 rows by themselves: 503 us
       // there, 508 when both halves are rescaled together.
       {
-        float mx[2];
+        float mx[NT];
+        bool grow = false;
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
           mx[nt] = fmaxf(fmaxf(sc[nt][0], sc[nt][1]), sc[nt][2]);
 #pragma unroll
           for (int r = 3; r < 15; r += 2) mx[nt] = fmaxf(fmaxf(mx[nt], sc[nt][r]), sc[nt][r + 1]);
           mx[nt] = fmaxf(mx[nt], sc[nt][15]);
+          grow |= mx[nt] * a.c > m[nt] + TAU;
         }
-        if (__builtin_amdgcn_ballot_w64((mx[0] * a.c > m[0] + TAU) | (mx[1] * a.c > m[1] + TAU))) {
+        if (__builtin_amdgcn_ballot_w64(grow)) {
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            if (!__builtin_amdgcn_ballot_w64(mx[nt] * a.c > m[nt] + TAU)) continue;
+          for (int nt = 0; nt < NT; ++nt) {
+            if (NT > 1 && !__builtin_amdgcn_ballot_w64(mx[nt] * a.c > m[nt] + TAU)) continue;
             const float mnew = fmaxf(m[nt], other_half_max(mx[nt]) * a.c);
             const float alpha = __builtin_amdgcn_exp2f(m[nt] - mnew);
             l[nt] *= alpha;
@@ -491,11 +509,11 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
         }
       }
       // P = 2^(S c - m) and O^T += V^T P^T, in two 16-key chunks
-      bf16x8 pa[2][2];
+      bf16x8 pa[2][NT];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
             pa[t][nt][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[nt][8 * t + e], a.c, -m[nt]));
@@ -503,11 +521,11 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
       h_static_for<NQ>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value, t = q / DT, dt = q % DT;
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
           o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[q % VA], pa[t][nt], o[nt][dt], 0, 0, 0);
         if constexpr (q + VA < NQ) vf[q % VA] = ld_v(q + VA);
       });
-      add_rows(pa, l);
+      add_rows<NT>(pa, l);
       if (!more) break;
       wait_vm<0>();
       h_barrier();
@@ -522,8 +540,8 @@ __global__ __launch_bounds__(128 * PACK) __attribute__((amdgpu_waves_per_eu(WPE,
     }
   }
 
-  merge_rows<D>(a, o, m, l, smem, wave, kh, lane, (size_t)b * a.Hq + head, hp > 1 ? 0 : qb * kBlk,
-                hp * a.S_q, seg);
+  merge_rows<D, NT>(a, o, m, l, smem, wave, kh, lane, (size_t)b * a.Hq + head,
+                    (hp > 1 ? 0 : qb * kBlk) + r0, hp * a.S_q, seg);
 }
 
 // Combines the segments of split lists: with M = max m_s over the segments and
@@ -567,24 +585,72 @@ __global__ __launch_bounds__(256) void k_attn_join(AttnArgs a) {
   }
 }
 
-template <int D, int PACK, int ST, int WPE>
+template <int D, int PACK, int RH, int ST, int WPE>
 static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
   if (a.S_k % kBlk != 0)
-    hipLaunchKernelGGL((k_attn_h<D, PACK, ST, true, WPE>), dim3(grid), dim3(128 * PACK), 0, s, a);
+    hipLaunchKernelGGL((k_attn_h<D, PACK, RH, ST, true, WPE>), dim3(grid), dim3(128 * RH * PACK), 0, s, a);
   else
-    hipLaunchKernelGGL((k_attn_h<D, PACK, ST, false, WPE>), dim3(grid), dim3(128 * PACK), 0, s, a);
+    hipLaunchKernelGGL((k_attn_h<D, PACK, RH, ST, false, WPE>), dim3(grid), dim3(128 * RH * PACK), 0, s, a);
+}
+
+// 32-row waves (RH = 2) or 64-row waves, from the workgroups an XCD gets at
+// most.  64 rows halve the LDS reads and cost a workgroup half the waves, so
+// they are the better form once the chip is full; while it is not, a call lasts
+// as long as the chain of its longest list, and 32-row waves have the shorter
+// chain per tile.  At one tile in LDS (ST = 1) more workgroups fit a CU, at two
+// a tile's copy hides behind the one before it.  Single heads, us, by
+// workgroups per XCD, 64-row waves / 32-row waves:
+//   D = 64 (6 / 4 workgroups per CU), causal lists from an index: 64 of S =
+//   2048 41.6 / 26.4, 128 44.6 / 41.1, 256 62.2 / 59.6, 512 105.4 / 101.5;
+//   windows of 8 blocks: 320 38.3 / 35.5, 768 74.3 / 73.9; 24 heads S = 32768 10%
+//   (1,536) 434 / 447.  Dense, no index, S = 2048: 320 112 / 108, 384 126 / 128,
+//   causal 320 62 / 64, 384 72 / 77.  Just full with 64-row waves (161 to 192)
+//   equal lists run 65.7 / 67.7, causal ones from an index 58.1 / 44.1.
+//   D = 128 (4 of 64-row waves; 2 of 32-row waves with two tiles, 3 with one),
+//   causal lists from an index, S = 2048: 64 57.2 / 39.3 / 37.6, 128 65.5 / 56.1 /
+//   55.3, 192 82.1 / 78.2 / 75.3, 256 103.4 / 101.4 / 95.9; 512 tokens against
+//   4000, batch of 4 (64) 95.1 / 69.8 / 90.7.  Dense, no index, S = 2048: 96 63.9 /
+//   67.0 / 59.6, 128 76.5 / 82.8 / 81.4 (causal 54.2 / 51.1 / 46.6), 192 129.6 / 121.8 /
+//   113.2, 256 147 / 167 / 149.  An index does not tell whether its lists are of
+//   one length: windows of 8 blocks at 128 take 29.5 / 32.7 / 32.5 (S = 1024, where
+//   lists differ by less: 28.4 / 31.5 / 31.7, causal 39.2 / 39.4 / 38.0).  Decoding, 32
+//   heads, batch of 64, 2000 keys (256; HBM): 372 / 349 / 355.
+static bool rows32_d64(const AttnArgs& a, int per, bool equal) {
+  return per <= (a.coord ? 320 : 512) && !(equal && per > 160 && per <= 192);
+}
+static bool rows32_d128(const AttnArgs& a, int per, bool equal) {
+  const bool some = a.nKB > 16;
+  if (!a.coord) return per <= 256 && (some || per <= 112 || per > 128);
+  return per <= 96 || (per <= 128 ? !equal && some : per <= 192);
 }
 
 hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, hipStream_t s) {
   if (items <= 0) return hipSuccess;
   if (pack == 1) {
-    items = a.coord ? items * a.ns : items;
-    if (D == 64) launch_h<64, 1, 1, 3>(a, items, s);
-    else launch_h<128, 1, 1, 2>(a, items, s);
+    const int grid = a.coord ? items * a.ns : items, per = grid / 8;
+    // lists known to be of one length (but for a window's first blocks)
+    const bool equal = a.coord && (a.ns > 1 || a.nQB == 1 || !a.causal || a.win_blocks > 0);
+    if (D == 64) {
+      if (rows32_d64(a, per, equal)) launch_h<64, 1, 2, 2, 4>(a, grid, s);
+      else launch_h<64, 1, 1, 1, 3>(a, grid, s);
+    } else {
+      if (per <= 64 || (a.coord && a.nQB == 1 && per > 192)) launch_h<128, 1, 2, 2, 2>(a, grid, s);
+      else if (rows32_d128(a, per, equal)) launch_h<128, 1, 2, 1, 3>(a, grid, s);
+      else launch_h<128, 1, 1, 1, 2>(a, grid, s);
+    }
   } else {
+    // Pairs of heads: 16/8 heads S = 2048 causal from an index, 64-row / 32-row
+    // waves, by workgroups per XCD: D = 64 (3 / 2 per CU) 32 31.0 / 26.9, 64 33.1 /
+    // 31.9, 96 41.9 / 44.4; D = 128 (2 / 1) 32 42.6 / 37.4, 64 53.0 / 56.9.
     const int grid = (a.coord ? (items + 7) / 8 * 8 * a.ns : xcd_grid(items)) * (pack / 2);
-    if (D == 64) launch_h<64, 2, 2, 3>(a, grid, s);
-    else launch_h<128, 2, 2, 2>(a, grid, s);
+    const int per = (items + 7) / 8 * a.ns * (pack / 2);
+    if (D == 64) {
+      if (per <= 64) launch_h<64, 2, 2, 2, 4>(a, grid, s);
+      else launch_h<64, 2, 1, 2, 3>(a, grid, s);
+    } else {
+      if (per <= 32) launch_h<128, 2, 2, 2, 2>(a, grid, s);
+      else launch_h<128, 2, 1, 2, 2>(a, grid, s);
+    }
   }
   return hipGetLastError();
 }

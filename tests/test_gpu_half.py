@@ -207,3 +207,28 @@ def test_index_of_mask_tensors(B, Hq, Hkv, S_q, S_k, D, uniform):
             want = oracle.attention(q[b:b + 1, :, r0:r1], k[b:b + 1], v[b:b + 1],
                                     np.ascontiguousarray(m[b:b + 1, :, qb:qb + 1]), D ** -0.5, False, 64)
             check(out[b:b + 1, :, r0:r1], want, f"batch {b} block {qb}")
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,S_q,S_k,causal", [
+    (64, 3, 3, 130, 450, False), (64, 3, 3, 448, 448, True), (128, 3, 3, 130, 450, False),
+    (128, 3, 3, 448, 448, True), (64, 4, 2, 448, 450, True), (128, 4, 2, 448, 450, True),
+    (128, 2, 2, 900, 900, True),
+], ids=str)
+def test_waves_of_32_rows_equal_waves_of_64(D, Hq, Hkv, S_q, S_k, causal):
+    """One problem by itself (few workgroups: 32 query rows per wave) and as
+    part of a large batch (64): the same rows bit for bit, with an index and
+    without, a block's maxima growing in one half only."""
+    B = 1 + 8 * 900 // (Hkv * -(-S_q // 64))
+    q, k, v = small_qkv(23, 1, Hq, Hkv, S_q, S_k, D)
+    grow = (1.0 + 20.0 * torch.arange(S_k) / S_k)[None, None, :, None]
+    still = (torch.arange(S_q) // 32 % 2 == 0)[None, None, :, None]
+    q = torch.where(still, q.float() / 64, q.float()).to(torch.bfloat16).cuda()
+    k, v = (k.float() * grow).to(torch.bfloat16).cuda(), v.cuda()
+    many = [t.expand(B, -1, -1, -1).contiguous() for t in (q, k, v)]
+    mask = lambda b: torch.ones((b, Hq, -(-S_q // 64), -(-S_k // 64)), dtype=torch.uint8, device="cuda")
+    s = steel()
+    for with_index in (False, True):
+        one = s.attn_fwd(q, k, v, mask(1) if with_index else None, causal=causal)
+        all_ = s.attn_fwd(*many, mask(B) if with_index else None, causal=causal)
+        assert torch.equal(one.expand_as(all_), all_)
+    check(one, oracle.attention(q.cpu(), k.cpu(), v.cpu(), None, D ** -0.5, causal, 64), "one problem")
