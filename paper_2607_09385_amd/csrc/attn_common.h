@@ -36,9 +36,9 @@ struct AttnArgs {
   const float* f8_scale;    //   and the per-(b, g) inverse scales {1/s_k, 1/s_v}
   // Block mask from coordinates (every block, or with win_blocks > 0 the window
   // and sink blocks of Problem): nothing was indexed, rows and their live lists
-  // are computed in the kernel; units: head packs (or heads) per query block,
-  // range: their order (coord_range)
-  int coord, win_blocks, sink_blocks, units, range;
+  // are computed in the kernel; units: head packs (or heads) per query block, m of
+  // them per key/value group, range: their order (coord_range)
+  int coord, win_blocks, sink_blocks, units, m, range;
   // SplitPlan: segments per list, heads per tile, the batch's first unit, its
   // rows, and its partial results: O [ns][rows][D], then {m, l} [ns][rows]
   int ns, hp, unit0;
@@ -106,7 +106,7 @@ __device__ __forceinline__ int coord_items(const AttnArgs& a, int x) {
   return coord_items(a.units, a.nQB, a.range, x);
 }
 __device__ __forceinline__ int coord_item(const AttnArgs& a, int x, int pos) {
-  return coord_item(a.units, a.nQB, a.range, x, pos);
+  return coord_item(a.units, a.nQB, a.range, a.m, x, pos);
 }
 
 __device__ __forceinline__ float other_half_max(float x) {

@@ -580,6 +580,7 @@ static hipError_t launch_split(const Problem& p, AttnArgs a, const SplitPlan& sp
   if (batch < 1) return hipErrorInvalidValue;
   a.ns = sp.ns;
   a.hp = sp.hp;
+  a.m = p.G / heads;
   a.part = part;
   for (int u = 0; u < sp.units; u += batch) {
     a.unit0 = u;
@@ -607,6 +608,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
     ap.order = w.order_p;
     ap.n_items = a.coord ? nullptr : w.n_items + kPackItems;  // 0 when they go with the single heads
     ap.units = p.B * (p.Hq / p.pack);
+    ap.m = p.G / p.pack;
     ap.range = coord_range(ap.units, p.nQB, p.causal, p.win_blocks > 0, false);
     hipError_t e = hipSuccess;
     if (D == 128 && p.pack == 4 && (size_t)p.S_q * D * 4 < (1ull << 31) && (PREC != kBf16 || p.NP > kFewPacks))
@@ -620,6 +622,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
   a.n_items = w.n_items;
   a.bucket = w.bucket;
   a.units = p.B * p.Hq;
+  a.m = p.G;
   a.range = coord_range(a.units, p.nQB, p.causal, p.win_blocks > 0, true);
   int grid = p.R;
   if (a.coord) {

@@ -12,8 +12,8 @@ SOURCE = """
 #include "internal.h"
 extern "C" {
 int items(int units, int nQB, int range, int x) { return steel::coord_items(units, nQB, range, x); }
-void order(int units, int nQB, int range, int x, int n, int* out) {
-  for (int i = 0; i < n; ++i) out[i] = steel::coord_item(units, nQB, range, x, i);
+void order(int units, int nQB, int range, int m, int x, int n, int* out) {
+  for (int i = 0; i < n; ++i) out[i] = steel::coord_item(units, nQB, range, m, x, i);
 }
 int range(int units, int nQB, int causal, int window, int single) {
   return steel::coord_range(units, nQB, causal, window, single);
@@ -33,10 +33,10 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(so)
 
 
-def share(lib, units, nQB, rng, x):
+def share(lib, units, nQB, rng, x, m=1):
     n = lib.items(units, nQB, rng, x)
     out = (ctypes.c_int * (n + 1))()
-    lib.order(units, nQB, rng, x, n + 1, out)
+    lib.order(units, nQB, rng, m, x, n + 1, out)
     assert out[n] == -1  # past the end
     return list(out[:n])
 
@@ -46,9 +46,10 @@ def test_every_item_once(lib, nQB):
     for units in list(range(1, 26)) + [36, 64, 100]:
         per = (units * nQB + 7) // 8  # positions the grids hold for an XCD
         for rng in [0] + [8 * r for r in range(1, (units + 7) // 8 + 1)]:
-            shares = [share(lib, units, nQB, rng, x) for x in range(8)]
-            assert all(len(s) <= per for s in shares)
-            assert sorted(i for s in shares for i in s) == list(range(units * nQB)), (units, rng)
+            for m in [m for m in (1, 2, 3, 5, 7) if units % m == 0]:
+                shares = [share(lib, units, nQB, rng, x, m) for x in range(8)]
+                assert all(len(s) <= per for s in shares)
+                assert sorted(i for s in shares for i in s) == list(range(units * nQB)), (units, rng, m)
 
 
 @pytest.mark.parametrize("units,nQB,causal,window,single", [
@@ -82,3 +83,16 @@ def test_ranges_are_of_about_one_size(lib, nQB, causal):
         r = lib.range(units, nQB, causal, False, True) // 8
         last = units // 8 % r or r
         assert 2 * last >= r or r - last <= units // 8 // r, (units, r, last)
+
+
+@pytest.mark.parametrize("groups", [8, 16, 64])
+@pytest.mark.parametrize("m", [2, 3, 5, 7])
+def test_units_of_a_group_share_an_xcd(lib, groups, m):
+    """Heads that read the same keys and values run on one XCD."""
+    units, nQB = groups * m, 16
+    rng = lib.range(units, nQB, False, False, True)
+    seen = {}
+    for x in range(8):
+        for i in share(lib, units, nQB, rng, x, m):
+            seen.setdefault(i // nQB // m, set()).add(x)
+    assert all(len(s) == 1 for s in seen.values())

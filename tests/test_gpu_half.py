@@ -102,6 +102,10 @@ def test_growing_maxima_of_one_half(D, half):
     (9, 17, 17, 960, 960, 64, False, 3, 1),
     (3, 50, 50, 900, 960, 128, True, 2, 1),
     (20, 32, 8, 900, 960, 64, False, 3, 1),
+    # groups of several units: dealt to the XCDs by group, eight and more of them
+    (2, 40, 8, 300, 400, 64, False, 3, 1),
+    (3, 28, 4, 300, 400, 128, True, 2, 1),
+    (2, 64, 8, 200, 400, 128, True, 2, 0),
 ], ids=lambda c: "x".join(str(int(v)) for v in c))
 def test_coordinates_equal_mask_tensor(shape):
     """Bit for bit where the lists are not split (fewer than 16 key blocks)."""
@@ -134,6 +138,7 @@ SPLIT = [
     (1, 4, 1, 200, 3000, 128, True),
     (1, 2, 2, 300, 1024, 64, False),
     (1, 1, 1, 1100, 1030, 128, True),  # dead rows at the start
+    (8, 40, 8, 13, 1024, 64, True),    # 320 units of one head, 5 per group
 ]
 
 
