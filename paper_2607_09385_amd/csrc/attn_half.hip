@@ -605,7 +605,8 @@ static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
 //   windows of 8 blocks: 320 38.3 / 35.5, 768 74.3 / 73.9; 24 heads S = 32768 10%
 //   (1,536) 434 / 447.  Dense, no index, S = 2048: 320 112 / 108, 384 126 / 128,
 //   causal 320 62 / 64, 384 72 / 77.  Just full with 64-row waves (161 to 192)
-//   equal lists run 65.7 / 67.7, causal ones from an index 58.1 / 44.1.
+//   equal lists run 65.7 / 67.7, causal ones from an index 58.1 / 44.1; decoding, 15/5
+//   heads, batch of 64, 6000 keys (160) 92.3 / 101.3.
 //   D = 128 (4 of 64-row waves; 2 of 32-row waves with two tiles, 3 with one),
 //   causal lists from an index, S = 2048: 64 57.2 / 39.3 / 37.6, 128 65.5 / 56.1 /
 //   55.3, 192 82.1 / 78.2 / 75.3, 256 103.4 / 101.4 / 95.9; 512 tokens against
@@ -616,7 +617,7 @@ static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
 //   lists differ by less: 28.4 / 31.5 / 31.7, causal 39.2 / 39.4 / 38.0).  Decoding, 32
 //   heads, batch of 64, 2000 keys (256; HBM): 372 / 349 / 355.
 static bool rows32_d64(const AttnArgs& a, int per, bool equal) {
-  return per <= (a.coord ? 320 : 512) && !(equal && per > 160 && per <= 192);
+  return per <= (a.coord ? 320 : 512) && !(equal && per > (a.nQB == 1 ? 136 : 160) && per <= 192);
 }
 static bool rows32_d128(const AttnArgs& a, int per, bool equal) {
   const bool some = a.nKB > 16;

@@ -170,9 +170,12 @@ SplitPlan plan_split(const Problem& p);
 // Up to this many head packs of 4 at D = 128 (bf16) are run two heads to a
 // workgroup (k_attn_h) instead of four (k_attn_ws): with one persistent
 // workgroup per CU and no more packs than CUs, CUs stand idle or wait for the
-// longest pack.  1000 queries against 11000 keys with 32/8 heads (128 packs):
-// 328 us by fours, 227 by twos; S = 4096 causal (512 packs) 126 by fours, 144
-// by twos.
+// longest pack.  Runs of plans, us, by fours / by twos: 64 packs causal S = 2048
+// 56.2 / 41.2, 128 packs 57.0 / 41.1, 192 57.6 / 51.0, 256 59.4 / 54.5, 384 64.2 / 72.8.
+// From 129 packs on lists of about one length go the other way (1536 queries
+// against 9000 keys, 192 packs 212.7 / 251.1; 128 packs 206.2 / 151.8; windows of 8
+// blocks S = 2048, 192 packs 27.2 / 29.2), which a plan does not tell, and by fours
+// the scaled Q is rounded to bf16: one line for both.
 constexpr int kFewPacks = 256;
 
 // Order of the items of a call without an index (unit * nQB + query block; a
@@ -186,8 +189,9 @@ constexpr int kFewPacks = 256;
 //   group (heads that read the same keys and values) are placed on one XCD, as
 //   long as eight groups are left (coord_unit).
 // range == 0: unit by unit, XCD x takes the x-th eighth.
-// (40/8 heads in single-head units D = 128, batch of 8, 1000 queries against 4000
-// keys: 1,055 us with the units of a group on five XCDs, 700 on one.)
+// (Single-head units D = 128, batch of 8, 1000 queries against 4000 keys, 40/8
+// heads: 1,055 us with the units of a group on all XCDs, 638 on one; batch of
+// 64, 17 queries, 727 and 428.)
 __host__ __device__ inline int coord_unit(int units, int m, int v) {
   if (m == 1 || v >= units / (8 * m) * (8 * m)) return v;
   const int b = v / (8 * m), in = v - b * (8 * m);
