@@ -80,11 +80,21 @@ typedef enum steel_status {
  * bitwise reproducible run to run.
  *
  * Without a mask tensor nothing is indexed and, unless the lists are split,
- * no scratch is used.  Calls without a mask tensor whose query blocks are too
- * few to fill the GPU (decoding, a few queries against many keys; S_k > 960)
- * run every live list in segments and add the partial results in fp32, and
- * heads of one group whose rows fit one block together as one item: the same
- * sums in another order.
+ * no scratch is used.  The result is bit for bit that of the same mask given
+ * as a tensor, but for two kinds of calls without a mask tensor, which take
+ * the same sums in another order (differences of the rounding of the softmax
+ * weights and, for packs of heads, of the scaled queries to bf16: up to 3e-3 of
+ * the output's norm):
+ *   split lists   query blocks too few to fill the GPU (decoding, a few
+ *                 queries against many keys; only where S_k > 960) run every
+ *                 live list in segments and add the partial results in fp32
+ *   shared tiles  with one query block (S_q <= 64) and several query heads per
+ *                 key/value head, heads of a group whose rows fit 64 rows
+ *                 together run as one item
+ * steel_attn_fwd_ex (without the fp8 flags), steel_attn_fwd_window and
+ * steel_attn_fwd_noalloc treat such calls as this one does, so without a mask
+ * tensor these calls agree with each other bit for bit; mask tensors and plans
+ * are never split and share no tiles.
  */
 int steel_attn_fwd(const void* q, const void* k, const void* v,
                    const uint8_t* block_mask, void* out,
@@ -124,7 +134,8 @@ int steel_block_index(const uint8_t* block_mask, int B, int Hq, int S_q, int S_k
  * calls (for example every layer of a model): steel_attn_plan builds the
  * live-block index once into caller-owned device workspace, steel_attn_run
  * runs the fused pass over it.  plan + run computes what steel_attn_fwd
- * computes, bit for bit unless that call splits its lists (see there).
+ * computes for the mask as a tensor, bit for bit; without one, bit for bit but
+ * for split lists and shared tiles (see there).
  *
  *   steel_attn_workspace_bytes  size of the workspace for these sizes, or 0
  *                               after an argument error (see
@@ -240,9 +251,9 @@ int steel_attn_merge(const float* o_parts, const float* lse_parts, int n_parts, 
  *  or kb < sink_blocks                   (sink blocks at the start)
  * and the causal structure is then applied exactly as for a mask tensor.  The
  * result is that of steel_attn_fwd / steel_attn_plan given that mask as a
- * [B][Hq][nQB][nKB] tensor, bit for bit unless the lists are split (see
- * steel_attn_fwd); no mask is read.  Every query head shares the
- * pattern, so head packs always run together.
+ * [B][Hq][nQB][nKB] tensor, bit for bit but for split lists and shared tiles
+ * (see steel_attn_fwd); no mask is read.  Every query head shares the pattern,
+ * so head packs always run together.
  *
  *   window_blocks  >= 1 (STEEL_ERR_INVALID_ARGUMENT otherwise)
  *   sink_blocks    >= 0

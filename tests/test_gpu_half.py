@@ -237,3 +237,62 @@ def test_waves_of_32_rows_equal_waves_of_64(D, Hq, Hkv, S_q, S_k, causal):
         all_ = s.attn_fwd(*many, mask(B) if with_index else None, causal=causal)
         assert torch.equal(one.expand_as(all_), all_)
     check(one, oracle.attention(q.cpu(), k.cpu(), v.cpu(), None, D ** -0.5, causal, 64), "one problem")
+
+
+def forms(q, k, v, causal):
+    """One problem without a mask tensor, in every form that takes none, and
+    as a mask tensor and plans."""
+    B, Hq, S_q, D = q.shape
+    Hkv, S_k = k.shape[1:3]
+    nQB, nKB = -(-S_q // 64), -(-S_k // 64)
+    s = steel()
+    other = torch.full((B, Hq, S_q, D), float("nan"), dtype=torch.float32, device="cuda")
+    st = s._lib.load().steel_attn_fwd_noalloc(
+        q.data_ptr(), k.data_ptr(), v.data_ptr(), None, other.data_ptr(), B, Hq, Hkv, S_q, S_k, D, 64,
+        D ** -0.5, int(causal), torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    ones = torch.ones((B, Hq, nQB, nKB), dtype=torch.uint8, device="cuda")
+    plain = {"fwd": s.attn_fwd(q, k, v, causal=causal),
+             "lse": s.attn_fwd_lse(q, k, v, causal=causal)[0],
+             "window": s.attn_fwd_window(q, k, v, nQB + nKB, nKB, causal=causal),
+             "noalloc": other}
+    indexed = {"mask": s.attn_fwd(q, k, v, ones, causal=causal),
+               "plan": s.Plan(None, B, Hq, Hkv, S_q, S_k, causal=causal).run(q, k, v),
+               "plan of mask": s.Plan(ones, B, Hq, Hkv, S_q, S_k, causal=causal).run(q, k, v)}
+    return plain, indexed
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S_q,S_k,D,causal,same", [
+    # one query block: a head per key/value head, and several (shared tiles), with
+    # packs of 4 at D = 128 beyond the 256 up to which two heads share a workgroup
+    (33, 8, 8, 1, 300, 64, True, True),
+    (5, 3, 3, 64, 900, 128, False, True),
+    (33, 32, 8, 1, 300, 128, True, False),
+    (3, 16, 8, 20, 900, 64, False, False),
+    (2, 6, 2, 21, 640, 128, True, False),
+    (2, 10, 2, 13, 700, 64, True, False),
+    # several query blocks, whole and split lists
+    (2, 8, 2, 65, 900, 128, True, True),
+    (1, 8, 2, 100, 3000, 64, True, False),
+    (70, 8, 1, 1, 2000, 128, True, False),
+], ids=str)
+def test_forms_agree(B, Hq, Hkv, S_q, S_k, D, causal, same):
+    """Without a mask tensor every call gives the same bits, an index (mask
+    tensor, plan) likewise; between the two bit for bit unless lists are split
+    or heads share a tile.  There both stay within the rounding of the weights
+    (and at D = 128 of the scaled Q) to bf16, 2^-9 each, of the same result:
+    2^-8 of the output's norm."""
+    q, k, v = (t.cuda() for t in small_qkv(29, B, Hq, Hkv, S_q, S_k, D))
+    plain, indexed = forms(q, k, v, causal)
+    for group in (plain, indexed):
+        first = next(iter(group.values()))
+        for name, out in group.items():
+            assert torch.equal(first, out), name
+    a, b = plain["fwd"], indexed["mask"]
+    if same:
+        assert torch.equal(a, b)
+    assert ((a - b).double().norm() / b.double().norm()).item() <= 2.0 ** -8
+    for h in (slice(0, 1), slice(B - 1, B)):
+        want = oracle.attention(q[h].cpu(), k[h].cpu(), v[h].cpu(), None, D ** -0.5, causal, 64)
+        check(a[h], want, "no mask tensor")
+        check(b[h], want, "mask tensor")
