@@ -296,3 +296,33 @@ def test_forms_agree(B, Hq, Hkv, S_q, S_k, D, causal, same):
         want = oracle.attention(q[h].cpu(), k[h].cpu(), v[h].cpu(), None, D ** -0.5, causal, 64)
         check(a[h], want, "no mask tensor")
         check(b[h], want, "mask tensor")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S_q,S_k", [
+    # partial results of 32.5 MiB and more (slots of D = 128 times 64 rows), above
+    # the fixed array's 32: shared tiles (the last unit a batch of its own), pairs
+    (8, 32, 8, 16, 8192),
+    (8, 16, 8, 64, 4096),
+], ids=str)
+def test_partial_results_in_batches(B, Hq, Hkv, S_q, S_k):
+    """steel_attn_fwd_noalloc takes the units in batches where steel_attn_fwd
+    takes them at once: bit for bit the same, every row written, and against the
+    oracle where the second batch begins and ends."""
+    D = 128
+    g = torch.Generator(device="cuda").manual_seed(31)
+    q, k, v = (torch.randn((B, h, n, D), generator=g, device="cuda").to(torch.bfloat16)
+               for h, n in ((Hq, S_q), (Hkv, S_k), (Hkv, S_k)))
+    s = steel()
+    want = s.attn_fwd(q, k, v)
+    out = torch.full((B, Hq, S_q, D), float("nan"), dtype=torch.float32, device="cuda")
+    st = s._lib.load().steel_attn_fwd_noalloc(
+        q.data_ptr(), k.data_ptr(), v.data_ptr(), None, out.data_ptr(), B, Hq, Hkv, S_q, S_k, D, 64,
+        D ** -0.5, 1, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    assert torch.isfinite(out).all()
+    assert torch.equal(out, want)
+    for g0 in (0, Hkv - 2, Hkv - 1):  # key/value groups of the last sequence
+        hq = slice(g0 * (Hq // Hkv), (g0 + 1) * (Hq // Hkv))
+        ref = oracle.attention(q[-1:, hq].cpu(), k[-1:, g0:g0 + 1].cpu(), v[-1:, g0:g0 + 1].cpu(), None,
+                               D ** -0.5, True, 64)
+        check(out[-1:, hq], ref, f"group {g0}")
