@@ -88,7 +88,6 @@ __global__ __launch_bounds__(attn_threads<PACK>()) void k_attn(AttnArgs a) {
   constexpr int KS = D / 16;       // k-steps of S^T = K Q^T (bf16)
   constexpr int KS8 = D / 64;      // k-steps of S^T = K Q^T (fp8)
   constexpr int DT = D / 32;       // d tiles of O^T
-  // E4M3 P needs the exact running maximum: rescale on every growth
   static_assert(LPW >= 1 && C % NW == 0 && CW8 >= 1 && CW8 <= NW && CW8 * 64 * LPW8 * 16 == TB8,
                 "tile copy split");
   // A ring of ST stages, each holding the K and the V tile of one key block:
@@ -187,11 +186,9 @@ __global__ __launch_bounds__(attn_threads<PACK>()) void k_attn(AttnArgs a) {
     issue_copy8(a.v8, at + TBK, kb);
   };
 
-  // Per-lane LDS read offsets in bytes (tile buffer base and the row block of
-  // each fragment are compile-time immediates; a key-half wave adds its half):
-  //   K fragment (sg, ks): row 32*sg + n, chunk (2*ks + hf)
-  //   V fragment (sg, t, cc, dt): row 32*sg + 16*t + 8*cc + 4*(tg>>1) + tr,
-  //                               chunk 4*dt + 2*(tg&1) + (tq>>1), half tq&1
+  // Per-lane LDS read offsets in bytes of the bf16 K tile (stage base and the
+  // row block of the sub-tile are added at use): K fragment (sg, ks) is row
+  // 32*sg + n, chunk 2*ks + hf.
   uint32_t koff[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) koff[ks] = (uint32_t)tile_elem<D>(n, 2 * ks + hf) * 2;
@@ -544,12 +541,16 @@ SplitPlan plan_split(const Problem& p) {
   const bool pair = sp.hp == 1 && p.pack > 1;
   const long long wgs = (long long)sp.units * p.nQB * (pair ? p.pack / 2 : 1);
   const int slots = half_slots(p.D, pair ? 2 : 1);
-  // Segments of at least 8 tiles (a segment also pays for its Q, its first
-  // tile's latency and its partial result, a few tiles' time; decoding 4
-  // sequences of 8000 keys takes 35.5 us with them, 41.3 with 4 tiles, 36.5
-  // with 16, and 140 unsplit with one head per tile).  One workgroup per CU is
-  // enough: 1000 queries against 11000 keys (256 workgroups) run 227 us whole
-  // and 244 in halves.  Lists of less than 16 tiles stay whole.
+  // Segments of at least 8 of the key blocks, or of the window's and sink's (a
+  // segment also pays for its Q, its first tile's latency and its partial
+  // result, a few tiles' time; decoding 4 sequences of 8000 keys with 64-row waves
+  // takes 35.5 us with them, 41.3 with 4 tiles, 36.5 with 16, and 140 unsplit with
+  // one head per tile).  One workgroup per CU is enough: 1000 queries against
+  // 11000 keys (256 workgroups) run 227 us whole and 244 in halves.  Less than 16
+  // key blocks stay whole.  The causal limit is not looked at: a causal_offset
+  // far below S_k - S_q leaves segments short or empty (32/8 heads D = 128, 64
+  // queries against 12000 keys with offset 0, one live tile each: 27.5 us, 31.3
+  // whole with an index).
   if (4 * wgs <= slots && p.nKB >= 16) {
     const long long live = p.win_blocks > 0 ? (long long)p.win_blocks + p.sink_blocks : p.nKB;
     const long long most = (live < p.nKB ? live : p.nKB) / 8;
