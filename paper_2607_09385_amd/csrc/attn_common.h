@@ -94,12 +94,14 @@ __device__ __forceinline__ LiveRow live_row(const AttnArgs& a, int row, int qb) 
   return r;
 }
 // Entry i < L of a live list: the key block, bit 31 set when it is partial.
-__device__ __forceinline__ uint32_t live_entry(const AttnArgs& a, const LiveRow& r, int qb, int i) {
-  if (!a.coord) return a.col[r.beg + i];
+__device__ __forceinline__ uint32_t coord_entry(const AttnArgs& a, const LiveRow& r, int qb, int i) {
   const int kb = i < r.a_len ? i : r.b0 + (i - r.a_len);
   const long long end = (long long)(kb + 1) * kBlk;
   const bool part = end > a.S_k || (a.causal && end - 1 > (long long)qb * kBlk + a.delta);
   return (uint32_t)kb | (part ? 0x80000000u : 0u);
+}
+__device__ __forceinline__ uint32_t live_entry(const AttnArgs& a, const LiveRow& r, int qb, int i) {
+  return a.coord ? coord_entry(a, r, qb, i) : a.col[r.beg + i];
 }
 
 __device__ __forceinline__ int coord_items(const AttnArgs& a, int x) {

@@ -134,9 +134,12 @@ __device__ __forceinline__ void lds_barrier() {
 }  // namespace
 
 // RAGGED: S_k is not a multiple of the block (the last key block's copies
-// clamp their rows); without it that path is compiled out.
+// clamp their rows); without it that path is compiled out.  GROUP: consecutive
+// items of the order per XCD; 0: items and live lists from coordinates.  (One
+// kernel for both spills 57 to 88 SGPRs, either by itself few or none.)
 template <bool RAGGED, int GROUP, int PREC>
 __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
+  constexpr bool COORD = GROUP == 0;
   constexpr bool QK8 = PREC == kFp8All;  // S = K Q^T from E4M3 operands
   constexpr bool PV8 = PREC != kBf16;    // O += V P from E4M3 operands
   constexpr int D = 128;
@@ -161,8 +164,8 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
 
-  if (!a.coord && !plan_matches(a)) return;  // index planned for another problem: out untouched
-  const int n_all = a.coord ? 0 : ((cint_p)a.n_items)[0];
+  if (!COORD && !plan_matches(a)) return;  // index planned for another problem: out untouched
+  const int n_all = COORD ? 0 : ((cint_p)a.n_items)[0];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -177,9 +180,9 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   struct Item {
     int L, beg, qb, b, h0;
   };
-  const int n_x = a.coord ? coord_items(a, xb)
-                          : (n_all / (8 * GROUP)) * GROUP +
-                                min(max(n_all % (8 * GROUP) - GROUP * xb, 0), GROUP);
+  constexpr int GR = COORD ? 1 : GROUP;
+  const int n_x = COORD ? coord_items(a, xb)
+                        : (n_all / (8 * GR)) * GR + min(max(n_all % (8 * GR) - GR * xb, 0), GR);
   const int K = (n_x + nwb - 1) / nwb;  // rounds of this XCD
   // round k of this workgroup: position r*nwb + w (even r) or r*nwb + nwb-1-w
   // (odd r) of the XCD's share of the work order, rounds in the order K-1,
@@ -198,13 +201,13 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
     w_item = -1;
     w_beg = 0;
     w_end = 0;
-    if (a.coord) {
+    if constexpr (COORD) {
       if (p >= 0) {
         w_item = coord_item(a, xb, p);
         w_end = coord_row(a, w_item % a.nQB).L;
       }
     } else {
-      const int idx = p < 0 ? n_all : xcd_slot<GROUP>(8 * p + xb);
+      const int idx = p < 0 ? n_all : xcd_slot<GR>(8 * p + xb);
       if (idx < n_all) {
         w_item = a.order[idx];
         const int r0 = (w_item / a.nQB) * 4 * a.nQB + w_item % a.nQB;
@@ -231,10 +234,8 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   };
   auto load_entry_vec = [&](const Item& it, int base) __attribute__((always_inline)) -> uint32_t {
     if (base + lane >= it.L) return 0u;
-    LiveRow r{};
-    if (a.coord) r = coord_row(a, it.qb);
-    else r.beg = it.beg;
-    return live_entry(a, r, it.qb, base + lane);
+    if constexpr (COORD) return coord_entry(a, coord_row(a, it.qb), it.qb, base + lane);
+    else return a.col[it.beg + base + lane];
   };
   auto kv_tile8 = [&](const Item& it) __attribute__((always_inline)) -> size_t {
     return ((size_t)it.b * a.Hkv + it.h0 / a.G) * a.nKB;
@@ -861,24 +862,21 @@ __global__ __launch_bounds__(512, 1) void k_attn_ws(AttnArgs a) {
   if (wu >= 0) pv_step(g - 1);
 }
 
-template <int PREC>
+template <bool RAGGED, int PREC>
 static void launch_ws(const AttnArgs& a, hipStream_t s) {
   const long long np = (long long)a.R / 4;
-  const bool few = np <= 4ll * 256;
-  // E4M3 tiles are padded with zero keys: only bf16 K or V tiles clamp
-  if (PREC != kFp8All && a.S_k % kBlk != 0) {
-    if (few) hipLaunchKernelGGL((k_attn_ws<true, 4, PREC>), dim3(256), dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_attn_ws<true, 16, PREC>), dim3(256), dim3(512), 0, s, a);
-  } else {
-    if (few) hipLaunchKernelGGL((k_attn_ws<false, 4, PREC>), dim3(256), dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_attn_ws<false, 16, PREC>), dim3(256), dim3(512), 0, s, a);
-  }
+  const dim3 grid(256), block(512);
+  if (a.coord) hipLaunchKernelGGL((k_attn_ws<RAGGED, 0, PREC>), grid, block, 0, s, a);
+  else if (np <= 4ll * 256) hipLaunchKernelGGL((k_attn_ws<RAGGED, 4, PREC>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_attn_ws<RAGGED, 16, PREC>), grid, block, 0, s, a);
 }
 
 hipError_t launch_attention_ws(const AttnArgs& a, int prec, hipStream_t s) {
-  if (prec == kFp8All) launch_ws<kFp8All>(a, s);
-  else if (prec == kFp8Pv) launch_ws<kFp8Pv>(a, s);
-  else launch_ws<kBf16>(a, s);
+  // E4M3 tiles are padded with zero keys: only bf16 K or V tiles clamp
+  const bool ragged = a.S_k % kBlk != 0;
+  if (prec == kFp8All) launch_ws<false, kFp8All>(a, s);
+  else if (prec == kFp8Pv) ragged ? launch_ws<true, kFp8Pv>(a, s) : launch_ws<false, kFp8Pv>(a, s);
+  else ragged ? launch_ws<true, kBf16>(a, s) : launch_ws<false, kBf16>(a, s);
   return hipGetLastError();
 }
 
