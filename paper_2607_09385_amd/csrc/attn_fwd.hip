@@ -546,8 +546,10 @@ SplitPlan plan_split(const Problem& p) {
   // result, a few tiles' time; decoding 4 sequences of 8000 keys with 64-row waves
   // takes 35.5 us with them, 41.3 with 4 tiles, 36.5 with 16, and 140 unsplit with
   // one head per tile).  One workgroup per CU is enough: 1000 queries against
-  // 11000 keys (256 workgroups) run 227 us whole and 244 in halves.  Less than 16
-  // key blocks stay whole.  The causal limit is not looked at: a causal_offset
+  // 11000 keys (256 workgroups) run 227 us whole and 244 in halves; 32 heads,
+  // batch of 16, one query against 8000 keys (512 workgroups) read their keys and
+  // values at 6 TB/s whole (D = 64 176 us, D = 128 349).  Less than 16 key blocks
+  // stay whole.  The causal limit is not looked at: a causal_offset
   // far below S_k - S_q leaves segments short or empty (32/8 heads D = 128, 64
   // queries against 12000 keys with offset 0, one live tile each: 27.5 us, 31.3
   // whole with an index).

@@ -7,32 +7,36 @@
 // a head runs the recurrence over keys 32 kh .. 32 kh + 31 of every tile with
 // its own (m, l, O), and the two states of a row are merged at the item's end.
 //
-// Why this split.  Per tile a wave issues D/4 MFMAs of 32x32x16 and the
-// softmax of 64 rows x 32 keys.  Measured on unrolled loops: an MFMA holds the
-// matrix core for 32 cycles and the wave's issue for 8, a wave issues other
-// VALU instructions every 4 cycles and exponentials every 8, so at D = 64 the
-// VALU (~130 instructions, 32 of them exponentials: ~650 cycles and 128 for
-// the MFMAs) bounds a tile before the matrix core (512 cycles), and at D = 128
-// both are near 1,000.  With all 64 rows in one wave a K or V fragment read
-// from LDS feeds two MFMAs (with 32 rows: one), which halves the LDS reads, and
-// the per-tile overhead (copies, list, waits) is paid once per 64 rows.  Half
-// the keys, because O (64 rows x D), Q and the scores of 64 keys do not fit the
-// 256 VGPRs that two waves per SIMD leave each.  At D = 64 three waves per SIMD
-// fit (162 VGPRs).
+// Why this split.  Per tile a wave of 64 rows issues D/4 MFMAs of 32x32x16 and
+// the softmax of 64 rows x 32 keys.  Measured on unrolled loops: an MFMA holds
+// the matrix core for 32 cycles and the wave's issue for 8, a wave issues other
+// VALU instructions every 4 cycles and exponentials every 8.  Counted (D = 64, the
+// 24-head S = 32768 top-10% workload): 198 VALU instructions per wave and tile,
+// about 150 of them on the common path (32 exponentials), the rest some 0.7
+// rescales of 32 rows and the item's start and end; 1,000 cycles of a SIMD's VALU
+// against 512 of its matrix core, 1,430 in all.  At D = 128 (Bernoulli masks): 196
+// instructions, 1,050 cycles of VALU, 1,024 of the matrix core, 2,590 in all.
+// With all 64 rows in one wave a K or V fragment read from LDS feeds two MFMAs
+// (with 32 rows: one), which halves the LDS reads, and the per-tile overhead
+// (copies, list, waits) is paid once per 64 rows.  Half the keys, because O (64
+// rows x D), Q and the scores of 64 keys do not fit the 256 VGPRs that two waves
+// per SIMD leave each.  At D = 64 three waves per SIMD fit (162 VGPRs).  Waves of
+// 32 rows (RH = 2) have the shorter chain per tile, for calls that do not fill the
+// chip; launch_attention_half has the line between the two.
 //
-// What it is near: on the 24-head S = 32768 top-10% workload the VALU is busy
-// three quarters of the time, the copies into LDS (16 KiB per tile and head,
-// 63 bytes per cycle and CU when they hit L2) a third, and the chip's power
-// limit holds the clock at 1.9 GHz.  Tried and not faster: rings private to a
-// wave without any barrier, deeper rings, two-stage rings for single heads
-// (fewer workgroups per CU), two waves per SIMD at D = 64.
+// What it is near: on the top-10% workload the VALU is busy 70% of the time, the
+// matrix core 36%, the copies into LDS (16 KiB per tile and head, 63 bytes per
+// cycle and CU when they hit L2) a third, and the chip's power limit holds the
+// clock at 1.9 GHz.  Tried and not faster: rings private to a wave without any
+// barrier, deeper rings, two-stage rings for single heads of 64-row waves (fewer
+// workgroups per CU), two waves per SIMD at D = 64, the first list entries loaded
+// beside the list's length or Q asked for before them (windows of one block, whose
+// items are all start and end: equal).
 //
 // Measured against the kernel it replaced (32 query rows per wave), whole
-// calls, with the maximum moved at 2^24 then: 24 heads S = 32768 D = 64 top-10%
-// 517 -> 485 us, 32 heads S = 8192 D = 128 Bernoulli masks 231 -> 215, 32/8 heads
-// S = 8192 D = 64 window (packs, prebuilt index) 184 -> 148.  With the changes
-// to index and calls since, and the maximum moved at 2^8: 498 -> 471, 222 ->
-// 191, 183 -> 144 (start and now in turn on one card).
+// calls, that library and this one in turn on one card: 24 heads S = 32768 D = 64
+// top-10% 518 -> 486 us, 32 heads S = 8192 D = 128 Bernoulli masks 229 -> 192, 32/8
+// heads S = 8192 D = 64 window (packs, prebuilt index) 183 -> 149.
 #include <cfloat>
 #include <utility>
 
@@ -602,8 +606,9 @@ static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
 // workgroups per XCD, 64-row waves / 32-row waves:
 //   D = 64 (6 / 4 workgroups per CU), causal lists from an index: 64 of S =
 //   2048 41.6 / 26.4, 128 44.6 / 41.1, 256 62.2 / 59.6, 512 105.4 / 101.5;
-//   windows of 8 blocks: 320 38.3 / 35.5, 768 74.3 / 73.9; 24 heads S = 32768 10%
-//   (1,536) 434 / 447.  Dense, no index, S = 2048: 320 112 / 108, 384 126 / 128,
+//   windows of 8 blocks: 320 38.3 / 35.5, 768 74.3 / 73.9; random 10%: 24 heads S =
+//   16384 (768) 122.4 / 120.1, 32/8 (1,024) 155 / 161, 24 heads S = 32768 (1,536) 434 /
+//   447.  Dense, no index, S = 2048: 320 112 / 108, 384 126 / 128,
 //   causal 320 62 / 64, 384 72 / 77.  Just full with 64-row waves (161 to 192)
 //   equal lists run 65.7 / 67.7, causal ones from an index 58.1 / 44.1; decoding, 15/5
 //   heads, batch of 64, 6000 keys (160) 92.3 / 101.3.
@@ -617,7 +622,7 @@ static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
 //   lists differ by less: 28.4 / 31.5 / 31.7, causal 39.2 / 39.4 / 38.0).  Decoding, 32
 //   heads, batch of 64, 2000 keys (256; HBM): 372 / 349 / 355.
 static bool rows32_d64(const AttnArgs& a, int per, bool equal) {
-  return per <= (a.coord ? 320 : 512) && !(equal && per > (a.nQB == 1 ? 136 : 160) && per <= 192);
+  return per <= (a.coord ? 320 : 800) && !(equal && per > (a.nQB == 1 ? 136 : 160) && per <= 192);
 }
 static bool rows32_d128(const AttnArgs& a, int per, bool equal) {
   const bool some = a.nKB > 16;

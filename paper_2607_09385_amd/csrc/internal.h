@@ -157,8 +157,8 @@ constexpr int kDemoteMinSingle = 1024;
 // (decoding, short chunks of queries against a long key cache), bf16 only:
 // every live list is cut into ns segments, each run by a workgroup of its own
 // that leaves its partial (m, l, O) in scratch, and k_attn_join combines them.
-// With a single query block the hp query heads of a group whose rows fit one
-// 64-row tile together are run as one item (hp = 1: one head per tile).
+// With a single query block, split or not, the hp query heads of a group whose
+// rows fit one 64-row tile together are run as one item (hp = 1: one head per tile).
 struct SplitPlan {
   int ns;             // segments per list (1: not split)
   int hp;             // query heads packed into one tile's rows

@@ -283,7 +283,8 @@ int check_workspace(const void* ws, size_t bytes, const Layout& L) {
 
 // The fused call once the arguments are checked: the stream's scratch buffer,
 // index build, attention.  Without a mask tensor there is no index, and in
-// bf16 no scratch: the attention kernels are all of the call.
+// bf16, unless the lists are split, no scratch: the attention kernels are all of
+// the call.
 int fused_call(const steel::Problem& p, const void* q, const void* k, const void* v,
                const uint8_t* block_mask, void* out, float* lse, float scale, void* stream) {
   int rc;
