@@ -210,8 +210,9 @@ template <int P> struct Par { static constexpr int value = P; };
 hipError_t launch_attention_ws(const AttnArgs& a, int prec, hipStream_t s);
 
 // bf16 forms: two waves per head, 64 query rows and half the keys of every
-// tile each (attn_half.hip); pack: heads per item of the list.
-hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, hipStream_t s);
+// tile each (attn_half.hip); pack: heads per item of the list; equal: the lists
+// are known to be of about one length (equal_lists).
+hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, bool equal, hipStream_t s);
 
 // Combines the partial results of one batch of units (attn_half.hip).
 hipError_t launch_attention_join(const AttnArgs& a, int D, hipStream_t s);

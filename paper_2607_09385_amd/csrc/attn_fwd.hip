@@ -592,7 +592,8 @@ static hipError_t launch_split(const Problem& p, AttnArgs a, const SplitPlan& sp
     a.part_rows = (long long)a.units * heads * p.S_q;
     a.row0 = (long long)u * heads * p.S_q;
     const int items = a.units * p.nQB;
-    hipError_t e = launch_attention_half(a, D, pack, pack == 1 ? (items + 7) / 8 * 8 : items, s);
+    hipError_t e = launch_attention_half(a, D, pack, pack == 1 ? (items + 7) / 8 * 8 : items,
+                                         sp.ns > 1 || equal_lists(p), s);
     if (e == hipSuccess && sp.ns > 1) e = launch_attention_join(a, D, s);
     if (e != hipSuccess) return e;
   }
@@ -612,11 +613,11 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
     ap.n_items = a.coord ? nullptr : w.n_items + kPackItems;  // 0 when they go with the single heads
     ap.units = p.B * (p.Hq / p.pack);
     ap.m = p.G / p.pack;
-    ap.range = coord_range(ap.units, p.nQB, p.causal, p.win_blocks > 0, false);
+    ap.range = coord_range(ap.units, p, false);
     hipError_t e = hipSuccess;
     if (D == 128 && p.pack == 4 && (size_t)p.S_q * D * 4 < (1ull << 31) && (PREC != kBf16 || p.NP > kFewPacks))
       e = launch_attention_ws(ap, PREC, s);
-    else if constexpr (PREC == kBf16) e = launch_attention_half(ap, D, p.pack, p.NP, s);
+    else if constexpr (PREC == kBf16) e = launch_attention_half(ap, D, p.pack, p.NP, false, s);
     else if (p.pack == 2) launch_one<D, 2, PREC>(ap, p.NP, s);
     else launch_one<D, 4, PREC>(ap, p.NP, s);
     if (e != hipSuccess) return e;
@@ -626,7 +627,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
   a.bucket = w.bucket;
   a.units = p.B * p.Hq;
   a.m = p.G;
-  a.range = coord_range(a.units, p.nQB, p.causal, p.win_blocks > 0, true);
+  a.range = coord_range(a.units, p, true);
   int grid = p.R;
   if (a.coord) {
     grid = (p.R + 7) / 8 * 8;
@@ -636,7 +637,7 @@ static hipError_t launch_d(const Problem& p, AttnArgs a, const IndexBuffers& w, 
     const long long per = (long long)p.nQB * p.G * ((p.B * p.Hkv + kBuckets - 1) / kBuckets);
     grid = (int)(kBuckets * per);
   }
-  if constexpr (PREC == kBf16) return launch_attention_half(a, D, 1, grid, s);
+  if constexpr (PREC == kBf16) return launch_attention_half(a, D, 1, grid, p.coord && equal_lists(p), s);
   else launch_one<D, 1, PREC>(a, grid, s);
   return hipGetLastError();
 }

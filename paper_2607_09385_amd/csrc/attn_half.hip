@@ -617,7 +617,8 @@ static void launch_h(const AttnArgs& a, int grid, hipStream_t s) {
 //   55.3, 192 82.1 / 78.2 / 75.3, 256 103.4 / 101.4 / 95.9; 512 tokens against
 //   4000, batch of 4 (64) 95.1 / 69.8 / 90.7.  Dense, no index, S = 2048: 96 63.9 /
 //   67.0 / 59.6, 128 76.5 / 82.8 / 81.4 (causal 54.2 / 51.1 / 46.6), 192 129.6 / 121.8 /
-//   113.2, 256 147 / 167 / 149.  An index does not tell whether its lists are of
+//   113.2, 256 147 / 167 / 149; 256 causal queries against 4096 keys (128, nearly equal
+//   lists) 176 / - / 217.  An index does not tell whether its lists are of
 //   one length: windows of 8 blocks at 128 take 29.5 / 32.7 / 32.5 (S = 1024, where
 //   lists differ by less: 28.4 / 31.5 / 31.7, causal 39.2 / 39.4 / 38.0).  Decoding, 32
 //   heads, batch of 64, 2000 keys (256; HBM): 372 / 349 / 355.
@@ -630,12 +631,10 @@ static bool rows32_d128(const AttnArgs& a, int per, bool equal) {
   return per <= 96 || (per <= 128 ? !equal && some : per <= 192);
 }
 
-hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, hipStream_t s) {
+hipError_t launch_attention_half(const AttnArgs& a, int D, int pack, int items, bool equal, hipStream_t s) {
   if (items <= 0) return hipSuccess;
   if (pack == 1) {
     const int grid = a.coord ? items * a.ns : items, per = grid / 8;
-    // lists known to be of one length (but for a window's first blocks)
-    const bool equal = a.coord && (a.ns > 1 || a.nQB == 1 || !a.causal || a.win_blocks > 0);
     if (D == 64) {
       if (rows32_d64(a, per, equal)) launch_h<64, 1, 2, 2, 4>(a, grid, s);
       else launch_h<64, 1, 1, 1, 3>(a, grid, s);

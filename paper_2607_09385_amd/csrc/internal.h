@@ -214,6 +214,20 @@ __host__ __device__ inline int coord_item(int units, int nQB, int range, int m, 
   return coord_unit(units, m, u0 + in - k * n) * nQB + (nQB - 1 - k);
 }
 
+// Whether the lists of a call without an index are of about one length: they
+// differ by a quarter of the longest at most (windows: but for their first
+// blocks).
+inline bool equal_lists(const Problem& p) {
+  if (!p.causal || p.win_blocks > 0) return true;
+  auto len = [&](long long row) {  // blocks up to the last key that the row sees
+    const long long end = row + p.delta + 1;
+    const long long n = end > 0 ? (end + kBlk - 1) / kBlk : 0;
+    return n < p.nKB ? n : p.nKB;
+  };
+  const long long most = len(p.S_q - 1), least = len(kBlk - 1 < p.S_q ? kBlk - 1 : p.S_q - 1);
+  return 4 * (most - least) <= most;
+}
+
 // The range, for an L2 of 4 MiB per XCD: the workgroups an XCD runs at one time
 // (32 to 192) should read the keys and values of few units.  Lists of equal
 // length (no causal limit) lose nothing by short ranges: 128 items per XCD.
@@ -222,6 +236,13 @@ __host__ __device__ inline int coord_item(int units, int nQB, int range, int m, 
 // limit: 2,315 us as one range, 1,206 with 128 items, 1,888 with 512 (an index
 // per call, head by head: 1,461); causal 1,155, 730 and 731 (956); batch of 8,
 // S = 4096, window of 16 blocks: 1,060, 674 and 742 (874).
+// Where lists are nearly equal, causal or not, a range also has no more units than
+// 8 MiB of keys and values, or 8: with few query blocks more of them lie so far
+// apart that they do not read a unit's keys together.  256 causal queries D = 64, with
+// 512 items / 128 (32 units) / 16 units / 8 (head by head): 40 heads, batch of 16, 2816
+// keys 255 / 182 / 168 / 173 us (203), 24 heads, 15616 keys 763 / 633 / 593 / 555
+// (570); 32 heads D = 128, batch of 16, 512 queries against 2048 keys, 512 items 474,
+// 8 units 322 (359).
 // The ranges are of about one size: a last one of few heads would begin the
 // heaviest lists when the others end (24 heads batch of 3 S = 4096 causal, 8 + 1
 // heads per XCD: 225 us at D = 64, 192 as one range of 9).
@@ -231,10 +252,18 @@ __host__ __device__ inline int coord_item(int units, int nQB, int range, int m, 
 // 155).  From 1,024 items on: below, a share without a unit's light first
 // blocks takes a round longer (282 items 18.8 -> 22.4 us).  Packs stay in ranges
 // (12/3 heads batch of 3 S = 4096: 83 us against 101).
-inline int coord_range(int units, int nQB, bool causal, bool window, bool single) {
+inline int coord_range(int units, const Problem& p, bool single) {
+  const int nQB = p.nQB;
+  const bool window = p.win_blocks > 0;
   if (window && single && units % 8 != 0 && units * nQB >= 1024) return 0;
-  const int items = causal || window ? 512 : 128;
-  const int per = (items + nQB - 1) / nQB, all = (units + 7) / 8;
+  const int items = p.causal || window ? 512 : 128;
+  int per = (items + nQB - 1) / nQB;
+  if (!window && equal_lists(p)) {
+    const int bytes = p.fp8 == kFp8All ? 2 : p.fp8 ? 3 : 4;  // of a key's and its value's element
+    const long long kv = ((long long)8 << 20) / ((long long)p.S_k * p.D * bytes);
+    if (kv < per) per = kv > 8 ? (int)kv : per < 8 ? per : 8;
+  }
+  const int all = (units + 7) / 8;
   const int n = (2 * all + per) / (2 * per);  // all / per, rounded to nearest
   return 8 * (n > 1 ? (all + n - 1) / n : all);
 }

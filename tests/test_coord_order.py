@@ -15,8 +15,20 @@ int items(int units, int nQB, int range, int x) { return steel::coord_items(unit
 void order(int units, int nQB, int range, int m, int x, int n, int* out) {
   for (int i = 0; i < n; ++i) out[i] = steel::coord_item(units, nQB, range, m, x, i);
 }
+static steel::Problem problem(int S_q, int S_k, int D, int causal, int delta, int win) {
+  steel::Problem p{};
+  p.S_q = S_q; p.S_k = S_k; p.D = D; p.causal = causal; p.delta = delta; p.win_blocks = win;
+  p.nQB = (S_q + 63) / 64; p.nKB = (S_k + 63) / 64;
+  return p;
+}
 int range(int units, int nQB, int causal, int window, int single) {
-  return steel::coord_range(units, nQB, causal, window, single);
+  return steel::coord_range(units, problem(64 * nQB, 64 * nQB, 64, causal, 0, window), single);
+}
+int range_of(int units, int S_q, int S_k, int D, int causal) {
+  return steel::coord_range(units, problem(S_q, S_k, D, causal, S_k - S_q, 0), 1);
+}
+int equal(int S_q, int S_k, int causal, int delta, int win) {
+  return steel::equal_lists(problem(S_q, S_k, 64, causal, delta, win));
 }
 }
 """
@@ -96,3 +108,36 @@ def test_units_of_a_group_share_an_xcd(lib, groups, m):
         for i in share(lib, units, nQB, rng, x, m):
             seen.setdefault(i // nQB // m, set()).add(x)
     assert all(len(s) == 1 for s in seen.values())
+
+
+@pytest.mark.parametrize("units,S_q,S_k,D", [(640, 256, 2816, 64), (384, 256, 15616, 64), (256, 256, 4096, 128),
+                                             (512, 512, 2048, 128), (1280, 128, 3000, 64)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_query_blocks_of_a_unit_run_together(lib, units, S_q, S_k, D, causal):
+    """Few query blocks against many keys: a unit's items lie within 1.5 ranges
+    of 8 MiB of keys and values (or 8 units) of each other, so that they read
+    them at one time."""
+    nQB = -(-S_q // 64)
+    most = max(8, (8 << 20) // (S_k * D * 4))
+    for x in range(8):
+        s = [i // nQB for i in share(lib, units, nQB, lib.range_of(units, S_q, S_k, D, causal), x)]
+        first, last = {}, {}
+        for at, u in enumerate(s):
+            first.setdefault(u, at)
+            last[u] = at
+        assert max(last[u] - first[u] for u in first) < 3 * most // 2 * nQB
+
+
+@pytest.mark.parametrize("S_q,S_k,causal,delta,win", [
+    (256, 2816, 1, 2560, 0), (512, 512, 1, 0, 0), (512, 2048, 1, 1536, 0), (1, 900, 1, 899, 0), (64, 900, 1, -30, 0),
+    (512, 700, 0, 0, 0), (512, 512, 1, 0, 3), (300, 900, 1, 2000, 0), (300, 900, 1, -400, 0), (300, 900, 1, 100, 0),
+    (100, 64, 1, -64, 0), (4096, 4096, 1, 0, 0), (1000, 12000, 1, 11000, 0), (1000, 12000, 1, -(1 << 30), 0),
+    (1000, 12000, 1, 1 << 30, 0)])
+def test_lists_of_about_one_length(lib, S_q, S_k, causal, delta, win):
+    nQB, nKB = -(-S_q // 64), -(-S_k // 64)
+    if causal and not win:
+        lens = [min(nKB, max(0, -(-(min(64 * qb + 63, S_q - 1) + delta + 1) // 64))) for qb in range(nQB)]
+        want = 4 * (max(lens) - min(lens)) <= max(lens)
+    else:
+        want = True
+    assert bool(lib.equal(S_q, S_k, causal, delta, win)) == want

@@ -106,6 +106,10 @@ def test_growing_maxima_of_one_half(D, half):
     (2, 40, 8, 300, 400, 64, False, 3, 1),
     (3, 28, 4, 300, 400, 128, True, 2, 1),
     (2, 64, 8, 200, 400, 128, True, 2, 0),
+    # few query blocks of nearly equal lists: ranges bounded by keys and values,
+    # and 64-row waves where 128 workgroups per XCD have lists of one length
+    (80, 8, 8, 130, 900, 64, True, 2, 0),
+    (32, 8, 8, 256, 1100, 128, True, 2, 0),
 ], ids=lambda c: "x".join(str(int(v)) for v in c))
 def test_coordinates_equal_mask_tensor(shape):
     """Bit for bit where the lists are not split (fewer than 16 key blocks)."""
