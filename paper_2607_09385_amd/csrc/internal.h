@@ -236,13 +236,13 @@ inline bool equal_lists(const Problem& p) {
 // limit: 2,315 us as one range, 1,206 with 128 items, 1,888 with 512 (an index
 // per call, head by head: 1,461); causal 1,155, 730 and 731 (956); batch of 8,
 // S = 4096, window of 16 blocks: 1,060, 674 and 742 (874).
-// Where lists are nearly equal, causal or not, a range also has no more units than
-// 8 MiB of keys and values, or 8: with few query blocks more of them lie so far
-// apart that they do not read a unit's keys together.  256 causal queries D = 64, with
+// Without a window a range also has no more units than 8 MiB of keys and values, or
+// 8 (16 where causal lists differ by more than a quarter): with few query blocks
+// more of them lie so far apart that they do not read a unit's keys together.  256 causal queries D = 64, with
 // 512 items / 128 (32 units) / 16 units / 8 (head by head): 40 heads, batch of 16, 2816
 // keys 255 / 182 / 168 / 173 us (203), 24 heads, 15616 keys 763 / 633 / 593 / 555
 // (570); 32 heads D = 128, batch of 16, 512 queries against 2048 keys, 512 items 474,
-// 8 units 322 (359).
+// 8 units 322 (359); 64 heads, 640 against 1280, 512 items 703, 16 units 489 (551).
 // The ranges are of about one size: a last one of few heads would begin the
 // heaviest lists when the others end (24 heads batch of 3 S = 4096 causal, 8 + 1
 // heads per XCD: 225 us at D = 64, 192 as one range of 9).
@@ -258,10 +258,12 @@ inline int coord_range(int units, const Problem& p, bool single) {
   if (window && single && units % 8 != 0 && units * nQB >= 1024) return 0;
   const int items = p.causal || window ? 512 : 128;
   int per = (items + nQB - 1) / nQB;
-  if (!window && equal_lists(p)) {
+  if (!window) {
+    const int least = equal_lists(p) ? 8 : 16;
     const int bytes = p.fp8 == kFp8All ? 2 : p.fp8 ? 3 : 4;  // of a key's and its value's element
     const long long kv = ((long long)8 << 20) / ((long long)p.S_k * p.D * bytes);
-    if (kv < per) per = kv > 8 ? (int)kv : per < 8 ? per : 8;
+    const int most = kv > least ? (int)(kv < per ? kv : per) : least;
+    if (most < per) per = most;
   }
   const int all = (units + 7) / 8;
   const int n = (2 * all + per) / (2 * per);  // all / per, rounded to nearest

@@ -111,14 +111,16 @@ def test_units_of_a_group_share_an_xcd(lib, groups, m):
 
 
 @pytest.mark.parametrize("units,S_q,S_k,D", [(640, 256, 2816, 64), (384, 256, 15616, 64), (256, 256, 4096, 128),
-                                             (512, 512, 2048, 128), (1280, 128, 3000, 64)])
+                                             (512, 512, 2048, 128), (1280, 128, 3000, 64),
+                                             (1024, 640, 1280, 128), (1024, 512, 768, 128)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_query_blocks_of_a_unit_run_together(lib, units, S_q, S_k, D, causal):
     """Few query blocks against many keys: a unit's items lie within 1.5 ranges
-    of 8 MiB of keys and values (or 8 units) of each other, so that they read
-    them at one time."""
+    of 8 MiB of keys and values (or 8 units, 16 of unequal lists) of each other,
+    so that they read them at one time."""
     nQB = -(-S_q // 64)
-    most = max(8, (8 << 20) // (S_k * D * 4))
+    least = 8 if lib.equal(S_q, S_k, causal, S_k - S_q, 0) else 16
+    most = max(least, (8 << 20) // (S_k * D * 4))
     for x in range(8):
         s = [i // nQB for i in share(lib, units, nQB, lib.range_of(units, S_q, S_k, D, causal), x)]
         first, last = {}, {}
